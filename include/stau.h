@@ -113,9 +113,11 @@ typedef struct stau_pencils stau_pencils;
  *          the single-block or the two-block sweep layout, as the FP64 solve
  *          uses), STAU_SOLVE_AUTO (FP64, the faster of the two at every size
  *          measured).  Else STAU_EINVAL.
- * factor_layout  storage of the factors the FP64 pencil solve reads (Sec. IX
- *          "Matrix solvers": the factors of the sparse banded pencil
- *          matrices are stored and reused while dt is fixed):
+ * factor_layout  storage of the banded factors that stau_solve and the steps of
+ *          pencils with a non-constant coefficient read (Sec. IX "Matrix
+ *          solvers": the factors of the sparse banded pencil matrices are
+ *          stored and reused while dt is fixed; the other steps' systems reduce
+ *          to tridiagonal ones, see stau_step):
  *          STAU_FACTORS_AUTO (where the solve streams its vectors through
  *          device memory, i.e. single-block layouts with more than 32 pencils
  *          per compute unit, the nonzero entries are also packed into sparse
@@ -216,7 +218,12 @@ int64_t stau_last_singular_pencil(const stau_pencils* pen);
  * B = sum_j c_j F~^{n-j} - a_j M~X^{n-j}, solves (a0 M~ + b0 L~) X~ = B per
  * pencil and recovers X = P^R X~.  Refactors (synchronously) when (a0, b0)
  * differ from the stored factorisation.  Updates st->X, st->hist and the
- * host fields iteration, dt_prev, head.  Asynchronous otherwise. */
+ * host fields iteration, dt_prev, head.  Asynchronous otherwise.
+ * Without a non-constant coefficient (and unless mixed_solve is
+ * STAU_SOLVE_REFINED) the pencil systems of the steps, the Runge-Kutta stages
+ * and stau_lbvp are solved exactly reduced to tridiagonal systems, whose
+ * factors are kept apart from those of stau_factor; the banded factors'
+ * storage is then allocated by the first call that needs it. */
 int stau_step(stau_pencils* pen, stau_state* st, double dt, void* stream);
 
 /* One IMEX Runge-Kutta step X^n -> X^{n+1} (Sec. IX "Runge-Kutta IMEX

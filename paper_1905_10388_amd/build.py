@@ -13,7 +13,7 @@ LIB = os.path.join(PKG, "libstau.so")
 # the check build: the same sources with the kernels' index checks compiled in
 # (STAU_CHECK_BOUNDS, reported by stau_check)
 LIB_CHECK = os.path.join(PKG, "libstau_check.so")
-SOURCES = ["stau.hip", "k_pencil.hip", "k_factor.hip", "k_evp.hip", "k_transform.hip", "k_xpass.hip",
+SOURCES = ["stau.hip", "k_tau.hip", "k_pencil.hip", "k_factor.hip", "k_evp.hip", "k_transform.hip", "k_xpass.hip",
            "k_adjoint.hip", "k_dctmm.hip", "k_grid.hip"]
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

@@ -55,6 +55,18 @@ struct SparseFactors {
   int strideF, strideB;
 };
 
+// Tridiagonal factors of the pencil solve without a non-constant coefficient
+// (k_tau.hip): one table of kTauArrays arrays of N doubles and kTauScal
+// scalars per distinct wavenumber modulus.
+constexpr int kTauArrays = 13, kTauScal = 14, kTauThreads = 256;
+struct TauFactors {
+  const int* slot;   // [P] table of a pencil slot, -1 for the inactive ones
+  const double* k;   // [nk] wavenumber moduli
+  double* tab;       // [nk][kTauArrays][N]
+  double* scal;      // [nk][kTauScal]
+  int nk, cus;       // tables, compute units of the device
+};
+
 struct XformArgs {
   int dim;
   int N, M;          // Chebyshev modes, dealiased z grid
@@ -151,6 +163,11 @@ hipError_t launch_sparse_records(const PencilArgs& a, const double* Lf, const ui
                                  const SparseFactors& sf, hipStream_t st);
 hipError_t launch_solve_sparse(const PencilArgs& a, const void* Bev, const SparseFactors& sf, void* X,
                                hipStream_t st);
+// The same solve by reduction to tridiagonal systems (k_tau.hip): a0 >= 0,
+// b0 = 1, no non-constant coefficient
+hipError_t launch_tau_factor(const PencilArgs& a, double a0, const TauFactors& tf, hipStream_t st);
+hipError_t launch_tau_solve(const PencilArgs& a, const TauFactors& tf, double a0, const void* Bev, void* X,
+                            hipStream_t st);
 // Mixed-precision solve with one FP64 refinement: FP32 sweeps on the FP32
 // factor copies, the FP64 residual of (a.refine_a0 M~ + a.refine_b0 L~) from
 // the templates, an FP32 correction sweep, the sum in FP64

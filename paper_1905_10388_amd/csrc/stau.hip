@@ -1,6 +1,7 @@
 // Host runtime behind the C ABI of include/stau.h: domain validation, FP64
 // twiddle / DCT tables (host libm, integer argument reduction), pencil system
 // description, device workspaces and the step sequence.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -249,6 +250,18 @@ struct stau_pencils {
   double last_a0 = 0.0, last_b0 = 0.0;
   double* tpl = nullptr;   // device: band templates of the operator (PencilArgs::tpl)
   double* ysp = nullptr;   // device: streamed-solve vectors (PencilArgs::ysp)
+  // tridiagonal factors of the step's operators (two slots, as the whole-band
+  // ones): the solve of every operator a0 M~ + L~, a0 >= 0, of pencils without
+  // a non-constant coefficient
+  struct TauSlot {
+    TauFactors f{};
+    bool valid = false;
+    double a0 = 0.0;
+    int64_t stamp = 0;
+  } tau[2];
+  bool tau_ok = false;
+  int* tau_slot = nullptr;     // device: TauFactors::slot
+  double* tau_k = nullptr;     // device: TauFactors::k
   // the step's factors also as sparse records (streamed solve), with their strides
   bool sparse_ok = false;
   SparseFactors sgeom{};
@@ -452,6 +465,16 @@ int stau_destroy_domain(stau_domain* dom) {
   return STAU_OK;
 }
 
+static void free_slot(stau_pencils::FactorSlot& f) {
+  for (void* q : {(void*)f.Lraw, (void*)f.sraw, (void*)f.Uraw, (void*)f.sf.F, (void*)f.sf.B, (void*)f.sf.lenF,
+                  (void*)f.sf.lenB, (void*)f.LTraw, (void*)f.UTraw, (void*)f.LBraw, (void*)f.UBraw, (void*)f.sTraw,
+                  (void*)f.sBraw, (void*)f.tLt, (void*)f.tLb, (void*)f.Rinv, (void*)f.E1, (void*)f.E2, (void*)f.tPt,
+                  (void*)f.tPb, (void*)f.L32raw, (void*)f.U32raw, (void*)f.LT32raw, (void*)f.UT32raw,
+                  (void*)f.LB32raw, (void*)f.UB32raw})
+    (void)hipFree(q);
+  f = stau_pencils::FactorSlot{};
+}
+
 static void free_pencils(stau_pencils* p) {
   if (p->side) (void)hipStreamDestroy(p->side);
   if (p->ev_fork) (void)hipEventDestroy(p->ev_fork);
@@ -471,19 +494,14 @@ static void free_pencils(stau_pencils* p) {
   hipFree(p->wvec);
   hipFree(p->rkbuf);
   for (auto* set : {p->slot, p->slotT, &p->evp})
-    for (int k = 0; k < (set == &p->evp ? 1 : 2); ++k) {
-      auto& f = set[k];
-      hipFree(f.Lraw);
-      hipFree(f.sraw);
-      hipFree(f.Uraw);
-      for (void* q : {(void*)f.sf.F, (void*)f.sf.B, (void*)f.sf.lenF, (void*)f.sf.lenB}) (void)hipFree(q);
-      for (void* q : {(void*)f.LTraw, (void*)f.UTraw, (void*)f.LBraw, (void*)f.UBraw, (void*)f.sTraw,
-                      (void*)f.sBraw, (void*)f.tLt, (void*)f.tLb, (void*)f.Rinv, (void*)f.E1,
-                      (void*)f.E2, (void*)f.tPt, (void*)f.tPb, (void*)f.L32raw, (void*)f.U32raw,
-                      (void*)f.LT32raw, (void*)f.UT32raw, (void*)f.LB32raw, (void*)f.UB32raw})
-        (void)hipFree(q);
-      f = stau_pencils::FactorSlot{};
-    }
+    for (int k = 0; k < (set == &p->evp ? 1 : 2); ++k) free_slot(set[k]);
+  for (auto& s : p->tau) {
+    hipFree(s.f.tab);
+    hipFree(s.f.scal);
+    s = stau_pencils::TauSlot{};
+  }
+  hipFree(p->tau_slot);
+  hipFree(p->tau_k);
   hipFree(p->tpl);
   hipFree(p->ysp);
   hipFree(p->evp_V);
@@ -576,6 +594,68 @@ static bool window_widths(PencilArgs& pa) {
   // backward windows of 32, 48 or 64 rows: the stored U columns are BW wide
   pa.BW = pa.kl + pa.ku + 1 <= 32 ? 32 : (pa.kl + pa.ku + 1 <= 48 ? 48 : 64);
   return pa.kl + 1 <= 32 && pa.kl + pa.ku + 1 <= 64;
+}
+
+// Whether the steps' pencil systems reduce to the tridiagonal solve: no
+// non-constant coefficient, not the refined mixed solve (whose FP32 sweeps are
+// asked for by name), and coefficients far from the range's ends (beyond, the
+// banded LU reports what is singular).
+static bool tau_range(double v) { return v > 1e-100 && v < 1e100; }
+static bool tau_applies(const stau_pencils* pen) {
+  const PencilArgs& a = pen->pa;
+  if (a.nncc > 0 || pen->refined) return false;
+  if (!tau_range(a.kappa) || !tau_range(a.nu) || !std::isfinite(a.buoyancy) || !std::isfinite(a.b_bottom) ||
+      !std::isfinite(a.b_top))
+    return false;
+  const double kx = a.two_pi_over_Lx, ky = a.two_pi_over_Ly;
+  if (!tau_range(kx * kx) || !tau_range(kx * kx * a.Px * a.Px / std::min(a.kappa, a.nu))) return false;
+  return a.desc.dim == 2 ||
+         (tau_range(ky * ky) && tau_range(ky * ky * (double)a.Ny * a.Ny / std::min(a.kappa, a.nu)));
+}
+
+// Wavenumber moduli (distinct values of kx^2 + ky^2: the factors depend on
+// nothing else) and the tables of both slots.
+static hipError_t tau_alloc(stau_pencils* pen, size_t* bytes) {
+  const PencilArgs& a = pen->pa;
+  const int Px = a.Px, Ny = a.desc.dim == 3 ? a.Ny : 1, N = a.desc.N;
+  std::vector<double> k2((size_t)a.P, -1.0);
+  for (int iy = 0; iy < Ny; ++iy) {
+    const int ky = iy < (Ny + 1) / 2 ? iy : iy - Ny;
+    const double y = a.two_pi_over_Ly * (double)ky;
+    if (a.desc.dim == 3 && iy == Ny / 2) continue;  // Nyquist slots stay inactive
+    for (int ix = 0; ix < Px - 1; ++ix) {
+      const double x = a.two_pi_over_Lx * (double)ix;
+      k2[(size_t)iy * Px + ix] = x * x + y * y;
+    }
+  }
+  std::vector<double> u;
+  for (double v : k2)
+    if (v >= 0.0) u.push_back(v);
+  std::sort(u.begin(), u.end());
+  u.erase(std::unique(u.begin(), u.end()), u.end());
+  std::vector<int> slot((size_t)a.P, -1);
+  for (size_t p = 0; p < slot.size(); ++p)
+    if (k2[p] >= 0.0) slot[p] = (int)(std::lower_bound(u.begin(), u.end(), k2[p]) - u.begin());
+  for (auto& v : u) v = std::sqrt(v);
+  hipError_t e = hipMalloc((void**)&pen->tau_slot, slot.size() * sizeof(int));
+  if (e == hipSuccess) e = hipMemcpy(pen->tau_slot, slot.data(), slot.size() * sizeof(int), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMalloc((void**)&pen->tau_k, u.size() * sizeof(double));
+  if (e == hipSuccess) e = hipMemcpy(pen->tau_k, u.data(), u.size() * sizeof(double), hipMemcpyHostToDevice);
+  const size_t nt = u.size() * kTauArrays * N * sizeof(double), ns = u.size() * kTauScal * sizeof(double);
+  int dev = 0, cus = 0;
+  if (e == hipSuccess) e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  for (auto& s : pen->tau) {
+    s.f.slot = pen->tau_slot;
+    s.f.k = pen->tau_k;
+    s.f.nk = (int)u.size();
+    s.f.cus = cus;
+    if (e == hipSuccess) e = hipMalloc((void**)&s.f.tab, nt);
+    if (e == hipSuccess) e = hipMalloc((void**)&s.f.scal, ns);
+    *bytes += nt + ns;
+  }
+  *bytes += slot.size() * sizeof(int) + u.size() * sizeof(double);
+  return e;
 }
 
 int stau_build_pencils(stau_domain* dom, const stau_rb_params* par, stau_pencils** out) {
@@ -833,15 +913,20 @@ int stau_build_pencils(stau_domain* dom, const stau_rb_params* par, stau_pencils
   if (e == hipSuccess && szGb) e = hipMalloc((void**)&pen->Gb, szGb);
   if (e == hipSuccess) e = hipMalloc((void**)&pen->wvec, (size_t)N * sizeof(double2));
   size_t szF = 0;
-  for (auto& f : pen->slot)
-    if (e == hipSuccess)
-      e = pen->two ? alloc_slot2(f, pen->pt, pen->pb, &szF, pen->refined)
-                   : alloc_slot(f, pa, &szF, pen->refined);
+  // pencils whose steps take the tridiagonal solve allocate the whole-band
+  // factors and their workspace when a call first needs them (band_storage)
+  pen->tau_ok = tau_applies(pen);
+  if (e == hipSuccess && pen->tau_ok) e = tau_alloc(pen, &szF);
+  if (e == hipSuccess && !pen->tau_ok)
+    for (auto& f : pen->slot)
+      if (e == hipSuccess)
+        e = pen->two ? alloc_slot2(f, pen->pt, pen->pb, &szF, pen->refined)
+                     : alloc_slot(f, pa, &szF, pen->refined);
   if (e == hipSuccess) e = hipMalloc((void**)&pen->sing, sizeof(int));
   if (e == hipSuccess) e = hipMalloc((void**)&pen->flag, sizeof(int));
   if (e == hipSuccess) e = hipMalloc((void**)&pen->scratch, szScratch);
   // the streamed single-block solve keeps each pencil's two real vectors here
-  const size_t szY = pen->two ? 0 : (size_t)pa.P * 2 * pa.nst * sizeof(double);
+  const size_t szY = pen->two || pen->tau_ok ? 0 : (size_t)pa.P * 2 * pa.nst * sizeof(double);
   if (e == hipSuccess && szY) e = hipMalloc((void**)&pen->ysp, szY);
   if (e != hipSuccess) {
     free_pencils(pen);
@@ -900,8 +985,45 @@ int stau_query(const stau_pencils* pen, stau_info* info) {
   return STAU_OK;
 }
 
+// Whole-band storage of a factor slot and (single-block layout) of the streamed
+// solve, on first use.
+static int band_storage(stau_pencils* pen, stau_pencils::FactorSlot* set, int k) {
+  auto& f = set[k];
+  const bool trans = set == pen->slotT;
+  size_t bytes = 0;
+  hipError_t e = hipSuccess;
+  if (!f.Lraw && !f.LTraw) {
+    if (trans)
+      e = pen->twoT ? alloc_slot2(f, pen->ptT, pen->pbT, &bytes) : alloc_slot(f, pen->paT, &bytes, false);
+    else
+      e = pen->two ? alloc_slot2(f, pen->pt, pen->pb, &bytes, pen->refined)
+                   : alloc_slot(f, pen->pa, &bytes, pen->refined);
+  }
+  if (e == hipSuccess && !trans && !pen->two && !pen->ysp) {
+    const size_t szY = (size_t)pen->pa.P * 2 * pen->pa.nst * sizeof(double);
+    e = hipMalloc((void**)&pen->ysp, szY);
+    if (e == hipSuccess) {
+      pen->pa.ysp = pen->ysp;
+      bytes += szY;
+    }
+  }
+  if (e != hipSuccess) {
+    free_slot(f);
+    (void)hipGetLastError();  // clear the failed allocation's error
+    return fail(STAU_ENOMEM, "factor allocation failed: %s", hipGetErrorString(e));
+  }
+  if (bytes && !trans && pen->tau_ok && pen->pa.ysp && pen->dom->d.factor_layout == STAU_FACTORS_AUTO)
+    pen->sparse_ok = sparse_records_apply(pen->pa, &pen->sgeom);
+  pen->ws_bytes += (int64_t)bytes;
+  return STAU_OK;
+}
+
 static int factor_into(stau_pencils* pen, stau_pencils::FactorSlot* set, const PencilArgs& pa,
                        int k, double a0, double b0, hipStream_t st) {
+  {
+    const int rc = band_storage(pen, set, k);
+    if (rc) return rc;
+  }
   auto& f = set[k];
   f.valid = false;
   f.sparse = false;
@@ -992,15 +1114,32 @@ static int factors_for(stau_pencils* pen, double a0, double b0, hipStream_t st,
   int k = set[0].stamp <= set[1].stamp ? 0 : 1;
   if (!set[0].valid) k = 0;
   else if (!set[1].valid) k = 1;
-  if (!set[k].Lraw && !set[k].LTraw) {  // (two-block slots are allocated with the pencils)
-    size_t bytes = 0;
-    hipError_t e = (trans && pen->twoT) ? alloc_slot2(set[k], pen->ptT, pen->pbT, &bytes)
-                                        : alloc_slot(set[k], pa, &bytes, !trans && pen->refined);
-    if (e != hipSuccess) return fail(STAU_ENOMEM, "factor allocation failed: %s", hipGetErrorString(e));
-    pen->ws_bytes += (int64_t)bytes;
-  }
   int rc = factor_into(pen, set, pa, k, a0, b0, st);
   if (rc) return rc;
+  *out = &set[k];
+  return STAU_OK;
+}
+
+// Tridiagonal factors of a0 M~ + b0 L~ (a cached slot if one matches, else the
+// least recently used one is refactored, synchronously); *out null where the
+// operator is not theirs: the whole-band factors then.
+static int tau_for(stau_pencils* pen, double a0, double b0, hipStream_t st, const stau_pencils::TauSlot** out) {
+  *out = nullptr;
+  if (!pen->tau_ok || b0 != 1.0 || !(a0 >= 0.0) || !(a0 < 1e100 * std::min(pen->pa.kappa, pen->pa.nu))) return STAU_OK;
+  auto* set = pen->tau;
+  int k = set[0].stamp <= set[1].stamp ? 0 : 1;
+  for (int q = 0; q < 2; ++q)
+    if (set[q].valid && set[q].a0 == a0) {
+      set[q].stamp = ++pen->clock;
+      *out = &set[q];
+      return STAU_OK;
+    }
+  set[k].valid = false;
+  HIP_TRY(timed(pen, K_FACTOR, st, [&] { return launch_tau_factor(pen->pa, a0, set[k].f, st); }));
+  HIP_TRY(hipStreamSynchronize(st));
+  set[k].valid = true;
+  set[k].a0 = a0;
+  set[k].stamp = ++pen->clock;
   *out = &set[k];
   return STAU_OK;
 }
@@ -1064,11 +1203,29 @@ static hipError_t explicit_term(stau_pencils* pen, const void* X, hipStream_t st
                [&] { return launch_ypass(pen->xa, -1, pen->pa.desc.ne, pen->G, pen->H, st, mixed); });
 }
 
-// Pencil solve of the step with the factors fs of (a0, b0): in mixed domains
-// with the refined solve, FP32 sweeps and one FP64 refinement; otherwise FP64,
-// the two-block solve where it applies, else the single-block solve.
-static hipError_t solve_launch(stau_pencils* pen, const stau_pencils::FactorSlot* fs, double a0,
+// Factors of (a0, b0) for the solve of a step, a stage or a boundary value
+// problem: tridiagonal where the operator has them, else whole-band.
+struct SolveFactors {
+  const stau_pencils::TauSlot* tau = nullptr;
+  const stau_pencils::FactorSlot* band = nullptr;
+};
+static int solve_factors(stau_pencils* pen, double a0, double b0, hipStream_t st, SolveFactors* out) {
+  int rc = tau_for(pen, a0, b0, st, &out->tau);
+  if (rc || out->tau) return rc;
+  stau_pencils::FactorSlot* f = nullptr;
+  rc = factors_for(pen, a0, b0, st, &f);
+  out->band = f;
+  return rc;
+}
+
+// Pencil solve with the factors of (a0, b0): the tridiagonal solve where it
+// applies; in mixed domains with the refined solve, FP32 sweeps and one FP64
+// refinement; otherwise FP64, the two-block solve where it applies, else the
+// single-block solve.
+static hipError_t solve_launch(stau_pencils* pen, const SolveFactors& sfac, double a0,
                                double b0, const double2* B, void* X, hipStream_t st, bool mixed) {
+  if (sfac.tau) return launch_tau_solve(pen->pa, sfac.tau->f, a0, B, X, st);
+  const stau_pencils::FactorSlot* fs = sfac.band;
   if (mixed && pen->refined && pen->two && fs->LfT32) {
     PencilArgs pt = pen->pt, pb = pen->pb;
     pt.refine_a0 = pb.refine_a0 = a0;
@@ -1098,9 +1255,9 @@ int stau_step(stau_pencils* pen, stau_state* s, double dt, void* stream) {
   HIP_TRY(hipSetDevice(pen->dom->d.device));
   double a0, a1, a2, b0, c1, c2;
   sbdf(s->iteration, dt, s->dt_prev, &a0, &a1, &a2, &b0, &c1, &c2);
-  stau_pencils::FactorSlot* fs = nullptr;
+  SolveFactors fs;
   {
-    int rc = factors_for(pen, a0, b0, st, &fs);
+    const int rc = solve_factors(pen, a0, b0, st, &fs);
     if (rc) return rc;
   }
   const int cur = s->head ^ 1;
@@ -1212,9 +1369,9 @@ int stau_step_rk(stau_pencils* pen, int scheme, double dt, void* X, void* stream
   const bool mixed = pen->dom->d.precision == STAU_MIXED;
   for (int i = 1; i <= s; ++i) {
     const double a0 = 1.0 / (dt * tb.H[i][i]), b0 = 1.0;
-    stau_pencils::FactorSlot* fs = nullptr;
+    SolveFactors fs;
     {
-      int rc = factors_for(pen, a0, b0, st, &fs);
+      const int rc = solve_factors(pen, a0, b0, st, &fs);
       if (rc) return rc;
     }
     k.stage = i;
@@ -1240,9 +1397,9 @@ int stau_lbvp(stau_pencils* pen, const void* F, void* X, void* stream) {
   if (!pen || !F || !X) return fail(STAU_EINVAL, "null argument");
   hipStream_t st = (hipStream_t)stream;
   HIP_TRY(hipSetDevice(pen->dom->d.device));
-  stau_pencils::FactorSlot* fs = nullptr;
+  SolveFactors fs;
   {
-    int rc = factors_for(pen, 0.0, 1.0, st, &fs);
+    const int rc = solve_factors(pen, 0.0, 1.0, st, &fs);
     if (rc) return rc;
   }
   HIP_TRY(launch_lbvp_rhs(pen->xa, F, pen->Bev, st));

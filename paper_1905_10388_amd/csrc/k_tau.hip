@@ -38,10 +38,9 @@
 // where a dense LU with partial pivoting has 7e-15 and 1e-10.
 //
 // Factor tables per distinct wavenumber modulus k (a 3-D domain of a square
-// box has one for up to eight pencils), kTauArrays arrays of N doubles: ratio,
-// 1 / u and the homogeneous fluxes (first flux 1) of b, of eta (and the normal
-// velocity) and of psi, then the unit-wall responses eta, psi, U and nu zeta;
-// and kTauScal scalars (TauScal).
+// box has one for up to eight pencils), kTauArrays arrays of N doubles: ratio and
+// 1 / u of b, of eta (and the normal velocity) and of psi, then the unit-wall
+// responses eta, psi, U and p; and kTauScal scalars (TauScal).
 #include <algorithm>
 
 #include "pencil.h"
@@ -50,11 +49,12 @@ namespace stau {
 
 namespace {
 
-// table arrays: three per system (b, eta, psi), then the unit-wall responses
-enum TauArray { kRatio = 0, kUi = 1, kPh = 2, kHe = 9, kHp, kHu, kHs };
-// scalars: k; per system the sums of the homogeneous q over the even and odd
-// degrees >= 1 and b_0; the sums of psi's homogeneous fluxes; the unit-wall sums of U
-enum TauScal { kScK = 0, kScSys = 1, kScPh = 10, kScU = 12 };
+// table arrays: two per system (b, eta, psi), then the unit-wall responses
+enum TauArray { kRatio = 0, kUi = 1, kHe = 6, kHp, kHu, kHpr };
+// scalars: k; per system the sums of the homogeneous q (first flux 1) over the
+// even and odd degrees >= 1 and b_0; the unit-wall sums of U; the mean pencil's
+// denominator of t
+enum TauScal { kScK = 0, kScSys = 1, kScU = 10, kScMean = 12 };
 
 __device__ __forceinline__ double cfac(int n) { return n == 0 ? 1.0 : 0.5; }
 
@@ -78,23 +78,24 @@ __device__ __forceinline__ double first_flux(int c, double G, double sig, double
 // tables leave as one contiguous copy.  A serial chain of N / 2 pairs of
 // divisions bounds it.
 // ---------------------------------------------------------------------------
+constexpr int kTauWork = 4;  // working arrays beside the tables: homogeneous fluxes, nu zeta
 __global__ void __launch_bounds__(kWave) tau_factor_kernel(int N, int nk, int KB, double a0, double kappa, double nu,
                                                            const double* __restrict__ kmod, double* __restrict__ tab,
                                                            double* __restrict__ scal) {
   extern __shared__ double lds[];
   const int lane = threadIdx.x;
   const int k0 = blockIdx.x * KB, nkb = min(KB, nk - k0);
-  const int KS = kTauArrays * N + kTauScal + 2;  // stride per wavenumber (staggers the banks)
+  const int KS = (kTauArrays + kTauWork) * N + kTauScal + 1;  // stride per wavenumber
   const int n = N / 2;
   {
     const int kb = lane / 6, sys = (lane % 6) >> 1, par = lane & 1;
     if (kb < nkb) {
       double* T = lds + (size_t)kb * KS;
-      double* sc = T + kTauArrays * N;
+      double* sc = T + (kTauArrays + kTauWork) * N;
       const double k = kmod[k0 + kb], k2 = k * k;
       const double x = sys == 0 ? (a0 + kappa * k2) / kappa : (sys == 1 ? (a0 + nu * k2) / nu : k2);
       const double x8 = 0.125 * x;
-      double *rat = T + (3 * sys + kRatio) * N, *ui = T + (3 * sys + kUi) * N, *ph = T + (3 * sys + kPh) * N;
+      double *rat = T + (2 * sys + kRatio) * N, *ui = T + (2 * sys + kUi) * N, *ph = T + (kTauArrays + sys) * N;
       double r2 = 1.0;  // ratio_{m+2}
       for (int j = n - 1; j >= 0; --j) {
         const int m = 2 * j + par;
@@ -112,16 +113,14 @@ __global__ void __launch_bounds__(kWave) tau_factor_kernel(int N, int nk, int KB
         r2 = u / (A + u);
         rat[m] = r2;
       }
-      double v = 1.0, H = 0.0, sum = par == 0 ? 1.0 : 0.0;
+      double v = 1.0, H = 0.0;
       for (int j = par == 0 ? 1 : 0; j < n; ++j) {
         const int m = 2 * j + par;
         H = fma(v, ui[m], H);
         v *= ph[m] * ui[m];
         ph[m] = v;
-        sum += v;
       }
       sc[kScSys + 3 * sys + par] = H;
-      if (sys == 2) sc[kScPh + par] = sum;
       if (sys == 0 && par == 0) sc[kScK] = k;
     }
   }
@@ -130,11 +129,12 @@ __global__ void __launch_bounds__(kWave) tau_factor_kernel(int N, int nk, int KB
     const int kb = lane >> 1, e = lane & 1;  // e: parity of eta, psi
     if (kb < nkb) {
       double* T = lds + (size_t)kb * KS;
-      double* sc = T + kTauArrays * N;
-      const double k2 = sc[kScK] * sc[kScK], al = a0 + nu * k2;
-      const double *uin = T + (3 + kUi) * N, *phn = T + (3 + kPh) * N;
-      const double *rp = T + (6 + kRatio) * N, *uip = T + (6 + kUi) * N, *php = T + (6 + kPh) * N;
-      double *he = T + kHe * N, *hp = T + kHp * N, *hu = T + kHu * N, *hs = T + kHs * N;
+      double* sc = T + (kTauArrays + kTauWork) * N;
+      const double k = sc[kScK], k2 = k * k, al = a0 + nu * k2;
+      const double *uin = T + (2 + kUi) * N, *phn = T + (kTauArrays + 1) * N;
+      const double *rp = T + (4 + kRatio) * N, *uip = T + (4 + kUi) * N, *php = T + (kTauArrays + 2) * N;
+      double *he = T + kHe * N, *hp = T + kHp * N, *hu = T + kHu * N, *hs = T + (kTauArrays + 3) * N;
+      double* hpr = T + kHpr * N;
       // eta with boundary sum 1, and nu zeta
       const double* hn = sc + kScSys + 3;
       const double st = first_flux(e, 1.0, 0.0, 0.0, hn);
@@ -167,7 +167,7 @@ __global__ void __launch_bounds__(kWave) tau_factor_kernel(int N, int nk, int KB
         v = b * (m + 2 < N ? uip[m + 2] : 0.0) * v + r2 * (ceta(m) / (4.0 * (m + 1)));
         hp[m] = v;
       }
-      double sig = 0.0, sphi = 0.0;
+      double sig = 0.0;
       v = 0.0;
       for (int j = 0; j < n; ++j) {
         const int m = 2 * j + e;
@@ -176,21 +176,43 @@ __global__ void __launch_bounds__(kWave) tau_factor_kernel(int N, int nk, int KB
         sig += (v + hp[m]) * uip[m];
         v = (b * v - 2.0 * m * hp[m]) * uip[m];
         if (m + 1 < N) hu[m + 1] = v;
-        sphi += v;
       }
       const double* hps = sc + kScSys + 6;
       const double sp = first_flux(e, 0.0, sig, hp[0], hps);
-      sc[kScU + e] = -2.0 * (sphi + sp * sc[kScPh + e]) - (e == 1 ? sp : 0.0);
-      double fl = sp;
+      double fl = sp, sum = 0.0;
       for (int j = 0; j < n; ++j) {
         const int m = 2 * j + e;
         hp[m] = m == 0 ? -sig - hps[0] * sp : (fl + hp[m]) * uip[m];
         if (m + 1 < N) {
           fl = hu[m + 1] + sp * php[m];
           hu[m + 1] = -2.0 * fl;
+          sum -= 2.0 * fl;
         }
       }
-      if (e == 1) hu[0] = -sp;
+      if (e == 1) {
+        hu[0] = -sp;
+        sum -= sp;
+        // t of the mean pencil: s_0 = a0 U_0 once sum U = 0
+        sc[kScMean] = hs[0] - a0 * (hu[0] - sum);
+      }
+      sc[kScU + e] = sum;
+      // p: D p = -a0 C w - nu k C eta where the degree exceeds k / 2, else k p = a0 U - s
+      for (int j = 0; j < n; ++j) {
+        const int m = 2 * j + 1 - e;
+        double p = 0.0;
+        if (m >= 1 && k < 2.0 * m) {
+          const int l = m - 1;
+          double ce = cfac(l) * he[l], cp = cfac(l) * hp[l];
+          if (l + 2 < N) {
+            ce -= 0.5 * he[l + 2];
+            cp -= 0.5 * hp[l + 2];
+          }
+          p = -k * (a0 * cp + nu * ce) / (2.0 * m);
+        } else if (k > 0.0) {
+          p = (a0 * hu[m] - hs[m]) / k;
+        }
+        hpr[m] = p;
+      }
     }
   }
   __syncthreads();
@@ -198,396 +220,385 @@ __global__ void __launch_bounds__(kWave) tau_factor_kernel(int N, int nk, int KB
   for (int kb = 0; kb < nkb; ++kb) {
     const double* T = lds + (size_t)kb * KS;
     for (int i = lane; i < per; i += kWave) tab[(size_t)(k0 + kb) * per + i] = T[i];
-    if (lane < kTauScal) scal[(size_t)(k0 + kb) * kTauScal + lane] = T[per + lane];
+    if (lane < kTauScal) scal[(size_t)(k0 + kb) * kTauScal + lane] = T[(kTauArrays + kTauWork) * N + lane];
   }
 }
 
 // ---------------------------------------------------------------------------
-// Serial passes of one lane over the degrees m = 2 j + c of its parity c of one
-// real part of complex arrays in LDS (pointers at that part; degree m at
-// [2 m]).  n = N / 2 elements (a power of two), taken in chunks whose loads are
-// issued one chunk ahead of the chain that consumes them: the chain is then
-// one FMA per degree, not an LDS latency.
+// Chains.  The N / 2 degrees m = 2 j + c of a parity c and real part of an array
+// are E consecutive j on each of L lanes of a row of 16 (L a power of two): both
+// recurrences run on registers, over the lane's own elements, then over the
+// lanes by a scan of (offset, factor) pairs, then over its elements again
+// from the value that enters it.  In LDS the four chains (parity, part) of an
+// array follow each other, lane blocks one double apart, so that the L lanes
+// read distinct banks.
 // ---------------------------------------------------------------------------
 namespace {
 
-constexpr int kTauCH = 8;
+// values of the lane d further up / down the row, of the row's lanes with one
+// bit of the lane index flipped
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+template <int D>
+__device__ __forceinline__ double from_up(double v) { return dpp<0x100 | D>(v); }
+template <int D>
+__device__ __forceinline__ double from_down(double v) { return dpp<0x110 | D>(v); }
 
-// load(j, buffer, slot) then step(j, buffer, slot) for j = n - 1 .. 0 (DOWN) or
-// 0 .. n - 1
-template <bool DOWN, typename LD, typename ST>
-__device__ __forceinline__ void tau_pass(int n, LD&& load, ST&& step) {
-  using B0 = std::integral_constant<int, 0>;
-  using B1 = std::integral_constant<int, 1>;
-  auto at = [&](int q, int i) { return DOWN ? n - 1 - (q * kTauCH + i) : q * kTauCH + i; };
-  if (n < kTauCH) {
-    for (int i = 0; i < n; ++i) {
-      load(at(0, i), B0{}, std::integral_constant<int, 0>{});
-      step(at(0, i), B0{}, std::integral_constant<int, 0>{});
-    }
-    return;
-  }
-  const int nc = n / kTauCH;
-  static_for<0, kTauCH>([&](auto i) { load(at(0, i), B0{}, i); });
-  for (int q = 0; q < nc; q += 2) {
-    if (q + 1 < nc) static_for<0, kTauCH>([&](auto i) { load(at(q + 1, i), B1{}, i); });
-    static_for<0, kTauCH>([&](auto i) { step(at(q, i), B0{}, i); });
-    if (q + 1 < nc) {
-      if (q + 2 < nc) static_for<0, kTauCH>([&](auto i) { load(at(q + 2, i), B0{}, i); });
-      static_for<0, kTauCH>([&](auto i) { step(at(q + 1, i), B1{}, i); });
-    }
-  }
+// sum over the L lanes of a chain, on all of them
+__device__ __forceinline__ double chain_sum(double v, int L) {
+  if (L > 1) v += dpp<0xB1>(v);   // lanes 1 apart
+  if (L > 2) v += dpp<0x4E>(v);   // pairs
+  if (L > 4) v += dpp<0x141>(v);  // quads (mirrored halves of eight)
+  if (L > 8) v += dpp<0x140>(v);  // halves of the row
+  return v;
 }
 
-// One chain: S holds ratio_{m+2} fh_m on entry and S_m on exit, F the particular
-// fluxes (first flux 0); bc = b, ui = 1 / u by degree.  Returns the sum of the
-// particular q over degrees >= 1, and the sum of F in *sumF.
-__device__ __forceinline__ double tau_chain(double* S, double* F, const double* bc, const double* ui, int n, int c,
-                                            double* sumF) {
-  {
-    double v = 0.0, up = 0.0;
-    double sv[2][kTauCH], bv[2][kTauCH], uv[2][kTauCH];
-    tau_pass<true>(
-        n,
-        [&](int j, auto b, auto i) {
-          const int m = 2 * j + c;
-          sv[b][i] = S[2 * m];
-          bv[b][i] = bc[m];
-          uv[b][i] = ui[m];
-        },
-        [&](int j, auto b, auto i) {
-          v = fma(bv[b][i] * up, v, sv[b][i]);
-          up = uv[b][i];
-          S[2 * (2 * j + c)] = v;
-        });
+// v_j = al_j v_{j+1} + s_j (UP) or v_j = al_j v_{j-1} + s_j: the value entering
+// this lane's block from its block's (offset v, factor pi); pi becomes the factor from
+// the chain's start to this block
+template <bool UP>
+__device__ __forceinline__ double chain_enter(double v, double& pi, int g, int L) {
+  auto level = [&](auto d) {
+    constexpr int D = decltype(d)::value;
+    if (D < L) {
+      const double v2 = UP ? from_up<D>(v) : from_down<D>(v), p2 = UP ? from_up<D>(pi) : from_down<D>(pi);
+      if (UP ? g + D < L : g >= D) {
+        v = fma(pi, v2, v);
+        pi *= p2;
+      }
+    }
+  };
+  level(std::integral_constant<int, 1>{});
+  level(std::integral_constant<int, 2>{});
+  level(std::integral_constant<int, 4>{});
+  level(std::integral_constant<int, 8>{});
+  const double in = UP ? from_up<1>(v) : from_down<1>(v), pin = UP ? from_up<1>(pi) : from_down<1>(pi);
+  const bool edge = UP ? g + 1 >= L : g == 0;
+  pi = edge ? 1.0 : pin;
+  return edge ? 0.0 : in;
+}
+
+// What a chain leaves beside q and its fluxes: first flux, q_0 (even q), sum of
+// the fluxes
+struct TauStart {
+  double2 f[2], q0, sum[2];
+};
+
+// One chain with boundary sum G: S (ratio_{m+2} fh_m) becomes q, F the fluxes;
+// bc = b, ui = 1 / u, h the system's scalars
+template <int E>
+__device__ __forceinline__ void tau_chain(double* S, double* F, const double* bc, const double* ui, const double* h,
+                                          double G, int g, int L, int c, int part, TauStart* out) {
+  const int o = g * (E + 1);
+  double s[E], b[E], u[E];
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    s[i] = S[o + i];
+    b[i] = bc[o + i];
+    u[i] = ui[o + i];
   }
-  double v = 0.0, sig = 0.0, sf = 0.0;
-  double sv[2][kTauCH], bv[2][kTauCH], uv[2][kTauCH];
-  tau_pass<false>(
-      n,
-      [&](int j, auto b, auto i) {
-        const int m = 2 * j + c;
-        sv[b][i] = S[2 * m];
-        bv[b][i] = bc[m];
-        uv[b][i] = ui[m];
-      },
-      [&](int j, auto b, auto i) {
-        const int m = 2 * j + c;
-        const double w = uv[b][i] * sv[b][i];
-        sig += fma(v, uv[b][i], w);
-        v = fma(bv[b][i] * uv[b][i], v, -(double)(2 * m) * w);
-        F[2 * m] = v;
-        sf += v;
-      });
-  *sumF = sf;
-  return sig;
+  const double un = g + 1 < L ? ui[o + E + 1] : 0.0;  // of the next lane's first degree
+  {
+    double v = 0.0, pi = 1.0;
+#pragma unroll
+    for (int i = E - 1; i >= 0; --i) {
+      const double al = b[i] * (i + 1 < E ? u[i + 1 < E ? i + 1 : i] : un);
+      v = fma(al, v, s[i]);
+      pi *= al;
+    }
+    v = chain_enter<true>(v, pi, g, L);
+#pragma unroll
+    for (int i = E - 1; i >= 0; --i) {
+      v = fma(b[i] * (i + 1 < E ? u[i + 1 < E ? i + 1 : i] : un), v, s[i]);
+      s[i] = v;
+    }
+  }
+  // upwards: be = b / u (1 at m = 0, whose flux is the first one)
+  const bool bottom = g == 0 && c == 0;
+  const int m0 = 2 * g * E + c;
+  const double S0 = chain_sum(g == 0 ? s[0] : 0.0, L);
+  double v = 0.0, pi = 1.0, sig = 0.0, hh = 0.0;
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    const double w = u[i] * s[i];
+    b[i] = i == 0 && bottom ? 1.0 : b[i] * u[i];
+    sig += fma(v, u[i], w);
+    hh = fma(pi, u[i], hh);
+    v = fma(b[i], v, -(double)(2 * (m0 + 2 * i)) * w);
+    pi *= b[i];
+  }
+  v = chain_enter<false>(v, pi, g, L);
+  sig = chain_sum(fma(hh, v, sig), L);
+  const double st = first_flux(c, G, sig, S0, h);
+  v = fma(pi, st, v);
+  double sum = 0.0;
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    const double q = (v + s[i]) * u[i];
+    v = fma(b[i], v, -(double)(2 * (m0 + 2 * i)) * (u[i] * s[i]));
+    sum += v;
+    S[o + i] = q;
+    F[o + i] = v;
+  }
+  sum = chain_sum(sum, L);
+  if (g == 0) {
+    if (c == 0) S[0] = G - sig - h[0] * st;
+    ((double*)&out->f[c])[part] = st;
+    ((double*)&out->sum[c])[part] = sum;
+  }
 }
 
 __device__ __forceinline__ double2 operator*(double s, double2 v) { return make_double2(s * v.x, s * v.y); }
 __device__ __forceinline__ double2 operator+(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ double2 operator-(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
 
-// A chain's results per (system, parity): first flux, and q_0 (even q)
-struct TauStart {
-  double2 f[2], q0;
-};
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
-// The solve: NP consecutive pencils per block of four wavefronts.  The
-// right-hand sides are read and the state is written over the degrees (every
-// access contiguous); the recurrences run one lane per (pencil, parity, real
-// part), independent systems on different wavefronts, in LDS.  LDS per
-// pencil: NA arrays of N complex (S and fluxes of b, then of psi; of eta; phi; g;
-// 3-D: of the normal velocity) and four of N doubles (b, 1 / u of b, then of
-// psi; of eta).
+// The solve: NP consecutive pencils per block, one (pencil, degree) per thread:
+// it reads its rows of the right-hand sides and its table entries at the start
+// and writes its nine (2-D: seven) state entries, every access contiguous over
+// the degrees; neighbouring degrees' values come from LDS.  The chains of the
+// independent systems run on different wavefronts.  LDS per pencil: NA arrays
+// (b and its fluxes, then psi's; eta's; phi; g; 3-D: the normal velocity's)
+// and four coefficient arrays (b, 1 / u of b, then of psi; of eta).
 // ---------------------------------------------------------------------------
-template <int DIM>
-__global__ void __launch_bounds__(kTauThreads) tau_solve_kernel(PencilArgs a, TauFactors tf, double a0, int NP,
-                                                                const double2* __restrict__ Bev,
-                                                                double2* __restrict__ X) {
+template <int DIM, int E>
+__global__ void __launch_bounds__(E > 8 ? 512 : 256) tau_solve_kernel(PencilArgs a, TauFactors tf, double a0, int NP,
+                                                                      int L, const double2* __restrict__ Bev,
+                                                                      double2* __restrict__ X) {
   constexpr int NA = DIM == 3 ? 8 : 6, S = DIM == 3 ? 9 : 7, ne = DIM == 3 ? 4 : 3;
   constexpr int eW = ne - 1;
   // state layout (p, b, u, [v], w, bz, uz, [vz], wz)
   constexpr int vP = 0, vB = 1, vU = 2, vV = 3, vW = ne, vBz = ne + 1, vUz = ne + 2, vVz = ne + 3, vWz = S - 1;
   enum { AB = 0, AZ, AE, AX, AF, AG, AT, ATZ };
   extern __shared__ double lds[];
-  const int N = a.desc.N, n = N / 2, tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int N = a.desc.N, tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int p0 = blockIdx.x * NP;
-  // per pencil: NA complex arrays and the coefficients, padded so that the
-  // pencils' lanes use different banks
-  const int PS = NA * 2 * N + 4 * N + 4;
-  double* inv = lds;                          // 1 / m, m <= N
-  TauStart* starts = (TauStart*)(inv + N + 2);  // [NP][4]: b, the normal velocity, eta, psi
-  double* sums = (double*)(starts + 4 * NP);  // [NP][parity][part]: sum of psi's particular fluxes
-  double* base = sums + 4 * NP;
-  for (int m = tid; m <= N; m += kTauThreads) inv[m] = m ? 1.0 / (double)m : 0.0;
-  auto arr = [&](int i, int which) { return (double2*)(base + (size_t)i * PS) + which * N; };
-  auto coef = [&](int i, int which) { return base + (size_t)i * PS + NA * 2 * N + which * N; };
-  struct Pen {
-    int slot;
-    double k, cx, cy;
-    bool mean;
+  const int PL = L * (E + 1);  // doubles per chain
+  const int PS = (NA * 4 + 8) * PL;
+  TauStart* starts = (TauStart*)lds;               // [NP][4]: b, the normal velocity, eta, psi
+  double2* gauge = (double2*)(starts + 4 * NP);    // the mean pencil's sum of p over degrees >= 1
+  double* base = (double*)(gauge + 1);
+  // chain ch = 2 parity + part of an array; coefficients by parity
+  auto chain_at = [&](int i, int which, int ch) { return base + (size_t)i * PS + (which * 4 + ch) * PL; };
+  auto coef_at = [&](int i, int which, int c) { return base + (size_t)i * PS + (NA * 4 + which * 2 + c) * PL; };
+  auto pos = [](int m) { return (m >> 1) + (m >> 1) / E; };
+
+  // this thread's pencil and degree
+  const int i = tid / N, m = tid - i * N, p = (int)blockIdx.x * NP + i;
+  const bool mine = i < NP && p < a.P;
+  const int slot = mine ? tf.slot[p] : -1;
+  const bool on = slot >= 0;
+  const double* T = tf.tab + (size_t)(on ? slot : 0) * (kTauArrays * N) + m;
+  const double* sc = tf.scal + (size_t)(on ? slot : 0) * kTauScal;
+  const double2 zero = make_double2(0.0, 0.0);
+  const double inv1 = 1.0 / (double)(m + 1), invm = m ? 1.0 / (double)m : 0.0;
+  double k = 0.0, cx = 1.0, cy = 0.0, r2[3], ui[3], he = 0.0, hp = 0.0, hu = 0.0, hpr = 0.0;
+  double2 fw = zero;
+  auto get = [&](int which, int l) {
+    const double* q = chain_at(i, which, 2 * (l & 1)) + pos(l);
+    return make_double2(q[0], q[PL]);
   };
-  auto pen = [&](int p) {
-    Pen q;
-    q.slot = p < a.P ? tf.slot[p] : -1;
-    q.k = q.slot >= 0 ? tf.scal[(size_t)q.slot * kTauScal + kScK] : 0.0;
-    q.cx = 1.0;
-    q.cy = 0.0;
-    q.mean = q.k == 0.0;
-    if (DIM == 3 && q.slot >= 0 && !q.mean) {
-      const int iy = p / a.Px, ix = p - iy * a.Px;
-      const int ky = iy < (a.Ny + 1) / 2 ? iy : iy - a.Ny;
-      q.cx = a.two_pi_over_Lx * (double)ix / q.k;
-      q.cy = a.two_pi_over_Ly * (double)ky / q.k;
-    }
-    return q;
+  auto put = [&](int which, double2 v) {
+    double* q = chain_at(i, which, 2 * (m & 1)) + pos(m);
+    q[0] = v.x;
+    q[PL] = v.y;
   };
-  auto rhs = [&](int p, int e, int m) -> double2 {  // row m of evolved equation e
-    return m <= N - 2 ? Bev[((size_t)p * ne + e) * N + m] : make_double2(0.0, 0.0);
+  // b_m and 1 / u_m of system sys into the coefficient arrays w, w + 1
+  auto coefs = [&](int sys, double x, int w) {
+    coef_at(i, w, m & 1)[pos(m)] = m + 1 < N ? 0.125 * x * inv1 * r2[sys] : 0.0;
+    coef_at(i, w + 1, m & 1)[pos(m)] = ui[sys];
   };
-  const int per = kTauArrays * N;
-  // b_m and 1 / u_m of a system into the coefficient arrays w, w + 1; returns
-  // ratio_{m+2}
-  auto coefs = [&](const double* T, int sys, double x, int i, int w, int m) {
-    const double r2 = m + 2 < N ? T[(3 * sys + kRatio) * N + m + 2] : 1.0;
-    coef(i, w)[m] = m + 1 < N ? 0.125 * x * inv[m + 1] * r2 : 0.0;
-    coef(i, w + 1)[m] = T[(3 * sys + kUi) * N + m];
-    return r2;
-  };
-  __syncthreads();
 
   // ---- right-hand sides of b, the normal velocity and phi ----
-  for (int idx = tid; idx < NP * N; idx += kTauThreads) {
-    const int i = idx / N, m = idx - i * N, p = p0 + i;
-    const Pen q = pen(p);
-    if (q.slot < 0) continue;
-    const double* T = tf.tab + (size_t)q.slot * per;
-    const double k2 = q.k * q.k, i4 = 0.25 * inv[m + 1];
-    const double2 fb = rhs(p, 0, m);
-    double2 fu = rhs(p, 1, m);
-    const double rb = coefs(T, 0, (a0 + a.kappa * k2) / a.kappa, i, 0, m);
-    const double rn = coefs(T, 1, (a0 + a.nu * k2) / a.nu, i, 2, m);
-    arr(i, AB)[m] = (rb * i4 / a.kappa) * fb;
+  if (on) {
+    const bool row = m <= N - 2;
+    const double2* B = Bev + (size_t)p * ne * N + m;
+    const double2 fb = row ? B[0] : zero, f1 = row ? B[N] : zero, f2 = DIM == 3 && row ? B[2 * N] : zero;
+    fw = row ? B[eW * N] : zero;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      r2[q] = m + 2 < N ? T[(2 * q + kRatio) * N + 2] : 1.0;
+      ui[q] = T[(2 * q + kUi) * N];
+    }
+    he = T[kHe * N];
+    hp = T[kHp * N];
+    hu = T[kHu * N];
+    hpr = T[kHpr * N];
+    k = sc[kScK];
+    if (DIM == 3 && k != 0.0) {
+      const int iy = p / a.Px, ix = p - iy * a.Px;
+      const int ky = iy < (a.Ny + 1) / 2 ? iy : iy - a.Ny;
+      cx = a.two_pi_over_Lx * (double)ix / k;
+      cy = a.two_pi_over_Ly * (double)ky / k;
+    }
+    const double k2 = k * k;
+    coefs(0, (a0 + a.kappa * k2) / a.kappa, 0);
+    coefs(1, (a0 + a.nu * k2) / a.nu, 2);
+    put(AB, (0.25 * inv1 * r2[0] / a.kappa) * fb);
+    double2 fu = f1;
     if (DIM == 3) {
-      const double2 fv = rhs(p, 2, m);
-      arr(i, AT)[m] = (rn * i4 / a.nu) * (q.cx * fv - q.cy * fu);
-      fu = q.cx * fu + q.cy * fv;
+      put(AT, (0.25 * inv1 * r2[1] / a.nu) * (cx * f2 - cy * f1));
+      fu = cx * f1 + cy * f2;
     }
     // U = i u_L: its row is i times that of u_L; phi_m = 2 row_m + phi_{m+2}
-    arr(i, AF)[m] = (m ? 2.0 : 1.0) * make_double2(-fu.y, fu.x);
-    arr(i, AG)[m] = rhs(p, eW, m);
+    put(AF, (m ? 2.0 : 1.0) * make_double2(-fu.y, fu.x));
   }
   __syncthreads();
 
-  // ---- serial: b; the normal velocity; phi ----
-  const int li = lane >> 2, c = (lane >> 1) & 1, part = lane & 1;
-  const Pen lq = pen(p0 + li);
-  const bool lane_on = li < NP && lq.slot >= 0;
-  const double* lsc = tf.scal + (size_t)(lane_on ? lq.slot : 0) * kTauScal;
-  // system sys in arrays (s, f) with coefficients w: the chain, its first flux
-  // and q_0 for the boundary sum G
-  auto chain = [&](int s, int f, int w, int sys, int slot, double G) {
-    double* Sp = (double*)arr(li, s) + part;
-    const double* h = lsc + kScSys + 3 * sys;
-    double sf;
-    const double sig = tau_chain(Sp, (double*)arr(li, f) + part, coef(li, w), coef(li, w + 1), n, c, &sf);
-    const double st = first_flux(c, G, sig, Sp[0], h);
-    double* o = (double*)(starts + li * 4 + slot);
-    o[2 * c + part] = st;
-    if (c == 0) o[4 + part] = G - sig - h[0] * st;
-    return sf;
+  // this lane's chain
+  const int ch = lane / L, g = lane - ch * L, li = ch >> 2, c = (ch >> 1) & 1, part = ch & 1;
+  const int lp = (int)blockIdx.x * NP + li;
+  const int lslot = li < NP && lp < a.P ? tf.slot[lp] : -1;
+  const double* lsc = tf.scal + (size_t)(lslot >= 0 ? lslot : 0) * kTauScal;
+  auto chain = [&](int s, int f, int w, int sys, int which, double G) {
+    tau_chain<E>(chain_at(li, s, ch & 3), chain_at(li, f, ch & 3), coef_at(li, w, c), coef_at(li, w + 1, c),
+                 lsc + kScSys + 3 * sys, G, g, L, c, part, starts + li * 4 + which);
   };
-  if (lane_on && wv == 0)
-    chain(AB, AZ, 0, 0, 0, lq.mean && part == 0 ? 0.5 * (a.b_top + (c ? -a.b_bottom : a.b_bottom)) : 0.0);
-  if (DIM == 3 && lane_on && wv == 1) chain(AT, ATZ, 2, 1, 1, 0.0);
-  if (lane_on && wv == 2) {
-    double* f = (double*)arr(li, AF) + part;
-    double z = 0.0, fv[2][kTauCH];
-    tau_pass<true>(
-        n, [&](int j, auto b, auto i) { fv[b][i] = f[2 * (2 * j + c)]; },
-        [&](int j, auto b, auto i) {
-          const int m = 2 * j + c;
-          z = m ? z + fv[b][i] : fma(0.5, z, fv[b][i]);
-          f[2 * m] = z;
-        });
-  }
-  __syncthreads();
-
-  // flux F_m (m >= 0) and q_m, qz_m of a system: particular plus first flux
-  // times homogeneous
-  auto flux = [&](const double2* F, const TauStart& s, const double* ph, int m) {
-    return F[m] + ph[m] * (m & 1 ? s.f[1] : s.f[0]);
-  };
-  auto q_of = [&](const double2* Sa, const double2* F, const TauStart& s, const double* T, int sys, double ui, int m) {
-    if (m == 0) return s.q0;
-    const double2 below = m == 1 ? s.f[1] : flux(F, s, T + (3 * sys + kPh) * N, m - 2);
-    return ui * (below + Sa[m]);
-  };
-  auto qz_of = [&](const double2* F, const TauStart& s, const double* T, int sys, int m) {
-    return m == 0 ? s.f[1] : 2.0 * flux(F, s, T + (3 * sys + kPh) * N, m - 1);
-  };
-
-  // ---- b and b_z leave; g = row of w + buoyancy C b ----
-  for (int idx = tid; idx < NP * N; idx += kTauThreads) {
-    const int i = idx / N, m = idx - i * N, p = p0 + i;
-    const Pen q = pen(p);
-    if (q.slot < 0) continue;
-    const double* T = tf.tab + (size_t)q.slot * per;
-    const TauStart& s = starts[i * 4];
-    const double2 *Sa = arr(i, AB), *F = arr(i, AZ);
-    const double* ui = coef(i, 1);
-    const double2 b = q_of(Sa, F, s, T, 0, ui[m], m);
-    X[((size_t)p * S + vB) * N + m] = b;
-    X[((size_t)p * S + vBz) * N + m] = qz_of(F, s, T, 0, m);
-    if (m <= N - 2) {
-      double2 cb = cfac(m) * b;
-      if (m + 2 < N) cb = cb - 0.5 * q_of(Sa, F, s, T, 0, ui[m + 2], m + 2);
-      arr(i, AG)[m] = arr(i, AG)[m] + a.buoyancy * cb;
+  if (lslot >= 0) {
+    if (wv == 0) {
+      const bool mean = lsc[kScK] == 0.0 && part == 0;
+      chain(AB, AZ, 0, 0, 0, mean ? 0.5 * (a.b_top + (c ? -a.b_bottom : a.b_bottom)) : 0.0);
+    }
+    if (DIM == 3 && wv == 1) chain(AT, ATZ, 2, 1, 1, 0.0);
+    if (wv == 2) {
+      double* f = chain_at(li, AF, ch & 3) + g * (E + 1);
+      double s[E], v = 0.0, pi = 1.0;
+#pragma unroll
+      for (int q = E - 1; q >= 0; --q) {
+        s[q] = f[q];
+        v += s[q];
+      }
+      // (the factor 1 / 2 of m = 0 reaches no other degree)
+      v = chain_enter<true>(v, pi, g, L);
+#pragma unroll
+      for (int q = E - 1; q >= 0; --q) {
+        v = q == 0 && g == 0 && c == 0 ? fma(0.5, v, s[q]) : v + s[q];
+        f[q] = v;
+      }
     }
   }
   __syncthreads();
 
-  // f_m / (4 nu (m + 1)) of eta with f_m = k g_m + 2 (m + 1) phi_{m+1}, m <= N - 2
-  auto fh_eta = [&](int i, double k, int m) {
-    return (1.0 / a.nu) * (0.25 * k * inv[m + 1] * arr(i, AG)[m] + 0.5 * arr(i, AF)[m + 1]);
-  };
-  // ---- right-hand side of eta ----
-  for (int idx = tid; idx < NP * N; idx += kTauThreads) {
-    const int i = idx / N, m = idx - i * N, p = p0 + i;
-    const Pen q = pen(p);
-    if (q.slot < 0) continue;
-    const double* T = tf.tab + (size_t)q.slot * per;
-    const double r2 = m + 2 < N ? T[(3 + kRatio) * N + m + 2] : 1.0;
-    arr(i, AE)[m] = m <= N - 2 ? r2 * fh_eta(i, q.k, m) : make_double2(0.0, 0.0);
+  // ---- b and b_z leave; g = row of w + buoyancy C b; right-hand side of eta ----
+  double2 gw = zero, fh = zero;  // g_m, f_m / (4 nu (m + 1)) of eta
+  const double k2 = k * k, al = a0 + a.nu * k2;
+  double2* Xp = X + (size_t)p * S * N + m;
+  if (on) {
+    const double2 b = get(AB, m);
+    Xp[vB * N] = b;
+    Xp[vBz * N] = m ? 2.0 * get(AZ, m - 1) : starts[i * 4].f[1];
+    if (m <= N - 2) {
+      double2 cb = cfac(m) * b;
+      if (m + 2 < N) cb = cb - 0.5 * get(AB, m + 2);
+      gw = fw + a.buoyancy * cb;
+      // f_m = k g_m + 2 (m + 1) phi_{m+1}
+      fh = (1.0 / a.nu) * (0.25 * k * inv1 * gw + 0.5 * get(AF, m + 1));
+    }
+    put(AG, gw);
+    put(AE, r2[1] * fh);
   }
   __syncthreads();
 
-  // ---- serial: eta with zero wall values ----
-  if (lane_on && wv == 0) chain(AE, AX, 2, 1, 2, 0.0);
+  // ---- eta with zero wall values; the mean pencil's gauge sum ----
+  if (wv == 0 && lslot >= 0) chain(AE, AX, 2, 1, 2, 0.0);
+  if (wv == 1 && blockIdx.x == 0) {  // (the mean pencil is the first)
+    double2 sum = zero;
+    for (int l = lane + 1; l < N; l += kWave) {
+      const double* q = chain_at(0, AG, 2 * ((l - 1) & 1)) + pos(l - 1);
+      sum = sum + (0.5 / (double)l) * make_double2(q[0], q[PL]);
+    }
+#pragma unroll
+    for (int d = 32; d; d >>= 1) {
+      sum.x += __shfl_xor(sum.x, d);
+      sum.y += __shfl_xor(sum.y, d);
+    }
+    if (lane == 0) *gauge = sum;
+  }
   __syncthreads();
 
   // ---- right-hand side of psi ----
-  for (int idx = tid; idx < NP * N; idx += kTauThreads) {
-    const int i = idx / N, m = idx - i * N, p = p0 + i;
-    const Pen q = pen(p);
-    if (q.slot < 0) continue;
-    const double* T = tf.tab + (size_t)q.slot * per;
-    const TauStart& s = starts[i * 4 + 2];
-    const double2 *Sa = arr(i, AE), *F = arr(i, AX);
-    const double k2 = q.k * q.k, al = a0 + a.nu * k2, d = (double)(m + 1);
-    const double r2 = coefs(T, 2, k2, i, 0, m);
-    double2 ce = make_double2(0.0, 0.0);
+  if (on) {
+    double2 ce = zero;
     if (m <= N - 2) {
       // C eta, from al C eta = f + nu D zeta where the differences of eta cancel
+      const double d = (double)(m + 1);
       if (al > 4.0 * a.nu * d * d) {
-        ce = (4.0 * a.nu * d / al) * (fh_eta(i, q.k, m) + flux(F, s, T + (3 + kPh) * N, m));
+        ce = (4.0 * a.nu * d / al) * (fh + get(AX, m));
       } else {
-        const double* ui = coef(i, 3);
-        ce = cfac(m) * q_of(Sa, F, s, T, 1, ui[m], m);
-        if (m + 2 < N) ce = ce - 0.5 * q_of(Sa, F, s, T, 1, ui[m + 2], m + 2);
+        ce = cfac(m) * get(AE, m);
+        if (m + 2 < N) ce = ce - 0.5 * get(AE, m + 2);
       }
     }
-    arr(i, AB)[m] = (0.25 * r2 * inv[m + 1]) * ce;
+    put(AB, (0.25 * r2[2] * inv1) * ce);
+    coefs(2, k2, 0);
   }
   __syncthreads();
 
-  // ---- serial: psi ----
-  if (lane_on && wv == 0) sums[li * 4 + c * 2 + part] = chain(AB, AZ, 0, 2, 3, 0.0);
-  __syncthreads();
-
-  // wall vorticity t of either class from sum U = 0; U0: the mean pencil's free
-  // constant of U
-  auto walls = [&](const Pen& q, int i, const double* T, double2* t, double2* U0) {
-    const double* sc = tf.scal + (size_t)q.slot * kTauScal;
-    const TauStart &s = starts[i * 4 + 3], &se = starts[i * 4 + 2];
-    *U0 = make_double2(0.0, 0.0);
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const double2 sf = make_double2(sums[i * 4 + e * 2], sums[i * 4 + e * 2 + 1]);
-      double2 su = -2.0 * (sf + sc[kScPh + e] * s.f[e]);
-      if (e == 1) su = su - s.f[1];
-      if (q.mean && e == 1) {  // s_0 = a0 U_0 with sum U = 0
-        const double den = T[kHs * N] - a0 * (T[kHu * N] - sc[kScU + 1]);
-        const double2 r = arr(i, AF)[0] + a.nu * se.f[1] + a0 * (s.f[1] + su);
-        t[1] = (-1.0 / den) * r;
-        *U0 = -1.0 * su - sc[kScU + 1] * t[1];
-      } else {
-        t[e] = (-1.0 / sc[kScU + e]) * su;
-      }
-    }
-  };
-  // ---- eta and psi in place of their S ----
-  for (int idx = tid; idx < NP * N; idx += kTauThreads) {
-    const int i = idx / N, m = idx - i * N, p = p0 + i;
-    const Pen q = pen(p);
-    if (q.slot < 0) continue;
-    const double* T = tf.tab + (size_t)q.slot * per;
-    double2 t[2], U0;
-    walls(q, i, T, t, &U0);
-    const double2 te = m & 1 ? t[1] : t[0];
-    arr(i, AE)[m] = q_of(arr(i, AE), arr(i, AX), starts[i * 4 + 2], T, 1, coef(i, 3)[m], m) + T[kHe * N + m] * te;
-    arr(i, AB)[m] = q_of(arr(i, AB), arr(i, AZ), starts[i * 4 + 3], T, 2, coef(i, 1)[m], m) + T[kHp * N + m] * te;
-  }
+  // ---- psi ----
+  if (wv == 0 && lslot >= 0) chain(AB, AZ, 0, 2, 3, 0.0);
   __syncthreads();
 
   // ---- velocity and pressure ----
-  for (int idx = tid; idx < NP * N; idx += kTauThreads) {
-    const int i = idx / N, m = idx - i * N, p = p0 + i;
-    if (p >= a.P) continue;
-    const Pen q = pen(p);
-    double2* Xp = X + (size_t)p * S * N + m;
-    if (q.slot < 0) {
+  if (!mine) return;
+  if (!on) {
 #pragma unroll
-      for (int v = 0; v < S; ++v) Xp[v * N] = make_double2(0.0, 0.0);
-      continue;
+    for (int v = 0; v < S; ++v) Xp[v * N] = zero;
+    return;
+  }
+  // wall vorticity t of either class from sum U = 0; U0: the mean pencil's free
+  // constant of U
+  const bool mean = k == 0.0;
+  const TauStart &se = starts[i * 4 + 2], &sp = starts[i * 4 + 3];
+  const double2 su0 = -2.0 * sp.sum[0], su1 = -2.0 * sp.sum[1] - sp.f[1];
+  double2 t0 = (-1.0 / sc[kScU]) * su0, t1, U0 = zero;
+  if (mean) {  // s_0 = a0 U_0 with sum U = 0
+    t1 = (-1.0 / sc[kScMean]) * (get(AF, 0) + a.nu * se.f[1] + a0 * (sp.f[1] + su1));
+    U0 = -1.0 * su1 - sc[kScU + 1] * t1;
+  } else {
+    t1 = (-1.0 / sc[kScU + 1]) * su1;
+  }
+  const double2 te = m & 1 ? t1 : t0, to = m & 1 ? t0 : t1;  // of the parity of m, of the other
+  const double2 psi = get(AB, m), eta = get(AE, m);
+  const double2 Up = m ? -2.0 * get(AZ, m - 1) : -1.0 * sp.f[1];
+  double2 U = Up + hu * to;
+  if (m == 0) U = U + U0;
+  const double2 w = k * (psi + hp * te), uz = eta + he * te - k * w;
+  // pressure: D p from the w rows where the degree exceeds k / 2, else from s
+  double2 pr = hpr * to;
+  if (m >= 1 && k < 2.0 * m) {
+    const int l = m - 1;
+    double2 ce = cfac(l) * get(AE, l), cp = cfac(l) * get(AB, l);
+    if (l + 2 < N) {
+      ce = ce - 0.5 * get(AE, l + 2);
+      cp = cp - 0.5 * get(AB, l + 2);
     }
-    const double* T = tf.tab + (size_t)q.slot * per;
-    const double2 *psi = arr(i, AB), *eta = arr(i, AE), *g = arr(i, AG);
-    const double k = q.k;
-    double2 t[2], U0;
-    walls(q, i, T, t, &U0);
-    const double2 to = m & 1 ? t[0] : t[1];  // of the class of U, p and s at this degree
-    double2 U = T[kHu * N + m] * to - qz_of(arr(i, AZ), starts[i * 4 + 3], T, 2, m);
-    if (m == 0) U = U + U0;
-    const double2 w = k * psi[m], uz = eta[m] - k * w;
-    // pressure: D p from the w rows where the degree exceeds k / 2, else from s
-    double2 pr = make_double2(0.0, 0.0);
-    if (m >= 1 && k < 2.0 * m) {
-      const int l = m - 1;
-      double2 ce = cfac(l) * eta[l], cp = cfac(l) * psi[l];
-      if (l + 2 < N) {
-        ce = ce - 0.5 * eta[l + 2];
-        cp = cp - 0.5 * psi[l + 2];
-      }
-      pr = 0.5 * inv[m] * (g[l] - (a0 * k) * cp - (a.nu * k) * ce);
-    } else if (!q.mean) {
-      const double2 s = arr(i, AF)[m] + a.nu * qz_of(arr(i, AX), starts[i * 4 + 2], T, 1, m) + T[kHs * N + m] * to;
-      pr = (1.0 / k) * (a0 * U - s);
-    } else {  // m = 0: gauge p(1) = 0 of the mean pencil
-#pragma unroll 8
-      for (int l = 1; l < N; ++l) pr = pr - 0.5 * inv[l] * g[l - 1];
-    }
-    Xp[vP * N] = pr;
-    Xp[vW * N] = w;
-    Xp[vWz * N] = (-k) * U;
-    // u_L = -i U
-    const double2 ul = make_double2(U.y, -U.x), uzl = make_double2(uz.y, -uz.x);
-    if (DIM == 3) {
-      const TauStart& s = starts[i * 4 + 1];
-      const double2 T0 = q_of(arr(i, AT), arr(i, ATZ), s, T, 1, coef(i, 3)[m], m);
-      const double2 Tz = qz_of(arr(i, ATZ), s, T, 1, m);
-      Xp[vU * N] = q.cx * ul - q.cy * T0;
-      Xp[vV * N] = q.cy * ul + q.cx * T0;
-      Xp[vUz * N] = q.cx * uzl - q.cy * Tz;
-      Xp[vVz * N] = q.cy * uzl + q.cx * Tz;
-    } else {
-      Xp[vU * N] = ul;
-      Xp[vUz * N] = uzl;
-    }
+    pr = pr + 0.5 * invm * (get(AG, l) - (a0 * k) * cp - (a.nu * k) * ce);
+  } else if (!mean) {
+    const double2 s = get(AF, m) + a.nu * (m ? 2.0 * get(AX, m - 1) : se.f[1]);
+    pr = pr + (1.0 / k) * (a0 * Up - s);
+  } else {  // m = 0: gauge p(1) = 0 of the mean pencil
+    pr = -1.0 * *gauge;
+  }
+  Xp[vP * N] = pr;
+  Xp[vW * N] = w;
+  Xp[vWz * N] = (-k) * U;
+  // u_L = -i U
+  const double2 ul = make_double2(U.y, -U.x), uzl = make_double2(uz.y, -uz.x);
+  if (DIM == 3) {
+    const double2 T0 = get(AT, m), Tz = m ? 2.0 * get(ATZ, m - 1) : starts[i * 4 + 1].f[1];
+    Xp[vU * N] = cx * ul - cy * T0;
+    Xp[vV * N] = cy * ul + cx * T0;
+    Xp[vUz * N] = cx * uzl - cy * Tz;
+    Xp[vVz * N] = cy * uzl + cx * Tz;
+  } else {
+    Xp[vU * N] = ul;
+    Xp[vUz * N] = uzl;
   }
 }
 
@@ -598,16 +609,10 @@ static void allow_lds(const void* fn, size_t bytes) {
   if (bytes > 65536) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-static size_t tau_lds_bytes(int dim, int N, int NP) {
-  const size_t pencil = ((dim == 3 ? 8 : 6) * 2 * N + 4 * N + 4) * sizeof(double) + 4 * sizeof(TauStart) +
-                        4 * sizeof(double);
-  return NP * pencil + (size_t)(N + 2) * sizeof(double);
-}
-
 hipError_t launch_tau_factor(const PencilArgs& a, double a0, const TauFactors& tf, hipStream_t st) {
   const int N = a.desc.N;
   // six lanes per wavenumber, at most half a compute unit's LDS per block
-  const size_t per = (size_t)(kTauArrays * N + kTauScal + 2) * sizeof(double);
+  const size_t per = (size_t)((kTauArrays + kTauWork) * N + kTauScal + 1) * sizeof(double);
   const int KB = (int)std::max<size_t>(1, std::min<size_t>(8, (size_t)(80 * 1024) / per));
   const size_t lds = KB * per;
   allow_lds((const void*)tau_factor_kernel, lds);
@@ -616,25 +621,37 @@ hipError_t launch_tau_factor(const PencilArgs& a, double a0, const TauFactors& t
   return hipGetLastError();
 }
 
-template <int DIM>
-static hipError_t launch_tau_solve_t(const PencilArgs& a, const TauFactors& tf, double a0, const void* Bev, void* X,
-                                     hipStream_t st) {
-  const int N = a.desc.N;
-  // pencils per block: as many as leave two blocks per compute unit, both in
-  // LDS (80 KB each) and in number
-  int NP = 8;
-  while (NP > 1 && (tau_lds_bytes(DIM, N, NP) > 80 * 1024 || (a.P + NP - 1) / NP < 2 * tf.cus)) NP >>= 1;
-  const size_t lds = tau_lds_bytes(DIM, N, NP);
-  allow_lds((const void*)tau_solve_kernel<DIM>, lds);
-  hipLaunchKernelGGL(tau_solve_kernel<DIM>, dim3((a.P + NP - 1) / NP), dim3(kTauThreads), lds, st, a, tf, a0, NP,
+template <int DIM, int E>
+static hipError_t launch_tau_solve_t(const PencilArgs& a, const TauFactors& tf, double a0, int NP, int L,
+                                     const void* Bev, void* X, hipStream_t st) {
+  constexpr int NA = DIM == 3 ? 8 : 6;
+  const int threads = E > 8 ? 512 : 256;
+  const size_t lds = NP * (4 * sizeof(TauStart) + (size_t)(NA * 4 + 8) * L * (E + 1) * sizeof(double)) + sizeof(double2);
+  if (NP * a.desc.N > threads) return hipErrorInvalidValue;
+  allow_lds((const void*)tau_solve_kernel<DIM, E>, lds);
+  hipLaunchKernelGGL((tau_solve_kernel<DIM, E>), dim3((a.P + NP - 1) / NP), dim3(threads), lds, st, a, tf, a0, NP, L,
                      (const double2*)Bev, (double2*)X);
   return hipGetLastError();
 }
 
 hipError_t launch_tau_solve(const PencilArgs& a, const TauFactors& tf, double a0, const void* Bev, void* X,
                             hipStream_t st) {
-  return a.desc.dim == 3 ? launch_tau_solve_t<3>(a, tf, a0, Bev, X, st)
-                         : launch_tau_solve_t<2>(a, tf, a0, Bev, X, st);
+  const int N = a.desc.N, n = N / 2;
+  // pencils per block: one (pencil, degree) per thread of 256 (at most eight
+  // pencils: 32 chains), fewer while that leaves compute units idle
+  int NP = std::min(8, std::max(1, 256 / N));
+  while (NP > 1 && (a.P + NP - 1) / NP < tf.cus) NP >>= 1;
+  // the 4 NP chains of a block share a wavefront: lanes per chain, degrees per lane
+  const int L = std::min(16 / NP, n), E = n / L;
+#define STAU_TAU(EE)                                                                              \
+  case EE:                                                                                        \
+    return a.desc.dim == 3 ? launch_tau_solve_t<3, EE>(a, tf, a0, NP, L, Bev, X, st)              \
+                           : launch_tau_solve_t<2, EE>(a, tf, a0, NP, L, Bev, X, st);
+  switch (E) {
+    STAU_TAU(1) STAU_TAU(2) STAU_TAU(4) STAU_TAU(8) STAU_TAU(16)
+  }
+#undef STAU_TAU
+  return hipErrorInvalidValue;
 }
 
 }  // namespace stau

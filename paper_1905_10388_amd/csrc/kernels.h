@@ -58,7 +58,7 @@ struct SparseFactors {
 // Tridiagonal factors of the pencil solve without a non-constant coefficient
 // (k_tau.hip): one table of kTauArrays arrays of N doubles and kTauScal
 // scalars per distinct wavenumber modulus.
-constexpr int kTauArrays = 13, kTauScal = 14, kTauThreads = 256;
+constexpr int kTauArrays = 10, kTauScal = 13;
 struct TauFactors {
   const int* slot;   // [P] table of a pencil slot, -1 for the inactive ones
   const double* k;   // [nk] wavenumber moduli

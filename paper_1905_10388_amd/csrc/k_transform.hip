@@ -11,6 +11,7 @@
 //   H[e][jz][p]                 complex, explicit term before the z forward
 //   F / Bev[p][e][n]            complex
 
+#include "fft.h"
 #include "xform.h"
 
 namespace stau {
@@ -268,7 +269,7 @@ __global__ void __launch_bounds__(kZThreads) zf_kernel(XformArgs a,
 // ys (0: the default above) replaces the output scale: 1 / Ngy of the forward
 // transform, 1 of the backward one (the adjoint grid transforms use the
 // other's).
-// NGC > 0: Ngy = NGC fixed at compile time, TK = PB / NGC (PB points per
+// NGC > 0 (FP32): Ngy = NGC fixed at compile time, TK = PB / NGC (PB points per
 // block, PB / 256 per thread).
 // ym (backward pass): output field f from input field ym.src[f], times i ky
 // where ym.der[f] (y derivatives formed here, after the z transform).
@@ -303,6 +304,8 @@ __global__ void __launch_bounds__(256) ypass_kernel(XformArgs a,
   const size_t inRows = DIR > 0 ? Ny : Ng, outRows = DIR > 0 ? Ng : Ny;
   const int fin = ym.n ? ym.src[f] : f;
   const bool dy = DIR > 0 && ym.n && ym.der[f];
+  // (tiles cover the active columns; forward the last one zeroes kx = Pa if that
+  // is beyond it, backward nothing reads it)
   const typename V2<T>::type* src = In + ((size_t)fin * M + jz) * inRows * Px;
   typename V2<T>::type* dst = Out + ((size_t)f * M + jz) * outRows * Px;
   // padded position -> stored slot (-1: padding or Nyquist)
@@ -351,9 +354,9 @@ __global__ void __launch_bounds__(256) ypass_kernel(XformArgs a,
   }
   __syncthreads();
   if constexpr (sizeof(T) == 8)
-    fft_lds_c<NGC, DIR, MAXBF, T, true, true>(buf, Ng, TK, (const cT*)a.twy, tid, nt);
+    fft_lds_c<NGC, DIR, MAXBF, T, true, NGC == 384>(buf, Ng, TK, (const cT*)a.twy, tid, nt);
   else
-    fft_lds_c<NGC, DIR, MAXBF, T, true, true>(buf, Ng, TK, (const cT*)a.twy32, tid, nt);
+    fft_lds_c<NGC, DIR, MAXBF, T, true, NGC == 384>(buf, Ng, TK, (const cT*)a.twy32, tid, nt);
   if (DIR > 0) {
     for (int idx = tid; idx < TK * Ng; idx += nt) {
       const int l = idx / TK, s = idx - l * TK;
@@ -373,7 +376,103 @@ __global__ void __launch_bounds__(256) ypass_kernel(XformArgs a,
       }
       stv<T>(dst + (size_t)iy * Px + kx, v);
     }
+    if (bx == (int)gridDim.x - 1 && k0 + TK < Px)
+      for (int iy = tid; iy < Ny; iy += nt) stv<T>(dst + (size_t)iy * Px + a.Pa, mk<T>(0, 0));
   }
+}
+
+// The FP64 y pass at the compile-time padded lengths NG = 3 Ny / 2 (fft_block):
+// TK active columns (kx < Pa) of one (field, z level) per block, from global
+// memory through the stages back to it, neighbouring columns on neighbouring
+// threads.  The padding third of the backward transform's first stage is zero at
+// compile time.  The column kx = Pa is left alone backward (nothing reads it) and
+// zeroed forward by the last tile.  Bound by the memory at the large sizes
+// (256x256x128: 491 us for 12 fields, 3.8 TB/s, as before) and by its latency
+// chain of a load, the stages and a store at the small ones, which lost its
+// integer divisions and half of its LDS passes: 32x32x32 21.7 -> 8.0 us,
+// 128x32x64 44 -> 14.8 us, 64x64x64 41 -> 16 us.  (A backward block that also
+// transforms the y derivative of its tile, from the spectrum held in
+// registers, measured 579 us at 256x256x128: fewer, longer blocks.)  FP32
+// keeps ypass_kernel, its length fixed too (128x128x128: 110 -> 88 us, the same
+// bits): registers to registers the compiler contracts products into sums in
+// other places, which FP32 results show (4e-6 of the history).
+constexpr int ytile(int NG) { return NG <= 96 ? 16 : NG == 192 ? 8 : 4; }
+constexpr int ythreads(int NG, int TK) {
+  const int n = (TK * fft_width(NG) + 63) / 64 * 64;
+  return n > 256 ? 256 : n;
+}
+
+template <int DIR, int NG, int TK = ytile(NG), int NT = ythreads(NG, TK)>
+__global__ void __launch_bounds__(NT) ypass_fft_kernel(XformArgs a, const double2* __restrict__ In,
+                                                       double2* __restrict__ Out, double ys, YMap ym) {
+  extern __shared__ double2 smem[];
+  using T = double;
+  using cT = cpx<T>;
+  cT* buf = (cT*)smem;
+  int bx = blockIdx.x, jz = blockIdx.y, f = blockIdx.z;
+  {
+    // a contiguous range of tiles per XCD (see ypass_kernel)
+    const int nbx = gridDim.x, nby = gridDim.y, total = nbx * nby * gridDim.z;
+    if (total % 8 == 0) {
+      int lin = bx + nbx * (jz + nby * f);
+      lin = (lin & 7) * (total >> 3) + (lin >> 3);
+      bx = lin % nbx;
+      lin /= nbx;
+      jz = lin % nby;
+      f = lin / nby;
+    }
+  }
+  constexpr int Ny = NG / 3 * 2, half = NG / 3;
+  constexpr int R0 = fft_radix(NG, 0), RL = fft_radix(NG, fft_stages(NG) - 1);
+  const int Px = a.Px, M = a.M, k0 = bx * TK, tid = threadIdx.x;
+  constexpr size_t inRows = DIR > 0 ? Ny : NG, outRows = DIR > 0 ? NG : Ny;
+  const int fin = ym.n ? ym.src[f] : f;
+  const bool dy = DIR > 0 && ym.n && ym.der[f];
+  const double2* src = In + ((size_t)fin * M + jz) * inRows * Px + k0;
+  double2* dst = Out + ((size_t)f * M + jz) * outRows * Px + k0;
+  const T scale_out = ys != 0.0 ? (T)ys : DIR > 0 ? (T)1 : (T)1 / (T)NG;
+  auto load = [&](int, int s, int j, cT* v) {
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      const int pos = j + r * (NG / R0);
+      v[r] = mk<T>(0, 0);
+      if constexpr (DIR > 0) {
+        if (3 * r >= R0 && 3 * r < 2 * R0) continue;  // padding
+        const bool hi = 3 * r >= R0;
+        if (k0 + s < a.Pa && (!hi || pos > NG - half)) {
+          v[r] = ldv<T>(src + (size_t)(hi ? pos + Ny - NG : pos) * Px + s);
+          if (dy) {  // i ky v
+            const T ky = (T)(a.two_pi_over_Ly * (double)(hi ? pos - NG : pos));
+            v[r] = mk<T>(-ky * v[r].y, ky * v[r].x);
+          }
+        }
+      } else {
+        if (k0 + s < a.Pa) v[r] = ldv<T>(src + (size_t)pos * Px + s);
+      }
+    }
+  };
+  auto store = [&](int s, int j, cT* v) {
+    if (k0 + s >= a.Pa) return;
+#pragma unroll
+    for (int r = 0; r < RL; ++r) {
+      const int pos = j + r * (NG / RL);
+      const cT o = scale(v[r], scale_out);
+      if constexpr (DIR > 0) {
+        stv<T>(dst + (size_t)pos * Px + s, o);
+      } else {
+        if (pos < half) stv<T>(dst + (size_t)pos * Px + s, o);
+        else if (pos > NG - half) stv<T>(dst + (size_t)(pos + Ny - NG) * Px + s, o);
+      }
+    }
+  };
+  if constexpr (DIR < 0) {
+    // Nyquist slots: the row iy = half and, by the last tile, the column kx = Pa
+    if (tid < TK && k0 + tid < a.Pa) stv<T>(dst + (size_t)half * Px + tid, mk<T>(0, 0));
+    if (bx == (int)gridDim.x - 1)
+      for (int iy = tid; iy < Ny; iy += NT) stv<T>(dst + (size_t)iy * Px + (a.Pa - k0), mk<T>(0, 0));
+  }
+  const cT* tw = (const cT*)a.twy;
+  fft_block<NG, DIR, TK, NT, true, true, T>(buf, tw, tid, load, store, [](int s, int i) { return i * TK + s; });
 }
 
 // ---------------------------------------------------------------------------
@@ -624,17 +723,38 @@ hipError_t launch_zf(const XformArgs& a, const void* H, void* out, const RhsArgs
 }
 
 
+template <int NG>
+static hipError_t launch_ypass_ct(const XformArgs& a, int dir, int nf, const void* In, void* Out, hipStream_t st,
+                                  bool fp32, double ys, const YMap& ym) {
+  if (fp32) {
+    // tiles of 32 (24 points), 16 or 3072 / NG columns
+    constexpr int TK = NG == 24 ? 32 : NG <= 192 ? 16 : 3072 / NG, PB = TK * NG, BF = (PB + 1023) / 1024;
+    auto fn = dir > 0 ? ypass_kernel<+1, BF, float, NG, PB> : ypass_kernel<-1, BF, float, NG, PB>;
+    hipLaunchKernelGGL(fn, dim3((a.Pa + TK - 1) / TK, a.M, nf), dim3(256), PB * sizeof(float2), st, a,
+                       (const float2*)In, (float2*)Out, TK, ys, ym);
+  } else {
+    constexpr int TK = ytile(NG), NT = ythreads(NG, TK);
+    auto fn = dir > 0 ? ypass_fft_kernel<+1, NG> : ypass_fft_kernel<-1, NG>;
+    hipLaunchKernelGGL(fn, dim3((a.Pa + TK - 1) / TK, a.M, nf), dim3(NT), TK * NG * sizeof(double2), st, a,
+                       (const double2*)In, (double2*)Out, ys, ym);
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_ypass(const XformArgs& a, int dir, int nf, const void* In, void* Out,
                         hipStream_t st, bool fp32, double ys, const YMap* map) {
   YMap ym{};
   if (map) ym = *map;
-  // Ny = 256 (384 padded points) with the length fixed at compile time; FP64
-  // tiles of 4 kx (1536 points, 24 KB of LDS: six blocks per compute unit
-  // instead of three with tiles of 8)
-  const bool c384 = a.Ngy == 384;
-  const int pb = c384 && !fp32 ? 1536 : 3072;
-  const int TK = a.Ngy >= pb ? 1 : pb / a.Ngy;
-  dim3 grid((a.Px + TK - 1) / TK, a.M, nf);
+  // the dealiased lengths of Ny = 16 .. 512; the other lengths (the scale-1
+  // transforms and the shortest and longest) at run time
+  if (2 * a.Ngy == 3 * a.Ny) {
+#define STAU_Y(NG) \
+  case NG: return launch_ypass_ct<NG>(a, dir, nf, In, Out, st, fp32, ys, ym);
+    switch (a.Ngy) { STAU_Y(24) STAU_Y(48) STAU_Y(96) STAU_Y(192) STAU_Y(384) STAU_Y(768) }
+#undef STAU_Y
+  }
+  const int TK = a.Ngy >= 3072 ? 1 : 3072 / a.Ngy;
+  dim3 grid((a.Pa + TK - 1) / TK, a.M, nf);
   const size_t lds = (size_t)TK * a.Ngy * (fp32 ? sizeof(float2) : sizeof(double2));
   auto go = [&](auto kern, auto in, auto out) {
     hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, a, in, out, TK, ys, ym);
@@ -644,18 +764,8 @@ hipError_t launch_ypass(const XformArgs& a, int dir, int nf, const void* In, voi
     using S2 = typename V2<TT>::type;
     const S2* in = (const S2*)In;
     S2* out = (S2*)Out;
-    if (c384) {
-      if constexpr (sizeof(TT) == 8) {
-        if (dir > 0) go(ypass_kernel<+1, 2, TT, 384, 1536>, in, out);
-        else go(ypass_kernel<-1, 2, TT, 384, 1536>, in, out);
-      } else {
-        if (dir > 0) go(ypass_kernel<+1, 3, TT, 384>, in, out);
-        else go(ypass_kernel<-1, 3, TT, 384>, in, out);
-      }
-    } else {
-      if (dir > 0) go(ypass_kernel<+1, 3, TT>, in, out);
-      else go(ypass_kernel<-1, 3, TT>, in, out);
-    }
+    if (dir > 0) go(ypass_kernel<+1, 3, TT>, in, out);
+    else go(ypass_kernel<-1, 3, TT>, in, out);
   };
   if (fp32) pick(std::common_type<float>());
   else pick(std::common_type<double>());

@@ -156,7 +156,7 @@ template <int M, int R, int NS, int DIR, typename T>
 __device__ __forceinline__ void fft_butterfly(cpx<T>* v, int j, const cpx<T>* __restrict__ tw) {
   if constexpr (NS > 1) {
     // powers from the table's entries 1 and 8 (at most three products deep)
-    cpx<T> w[R];
+    cpx<T> w[R > 8 ? 9 : R];
     const int t = (j % NS) * (M / (NS * R));
     w[1] = tw[t];
     if constexpr (R > 2) w[2] = cmul(w[1], w[1]);
@@ -166,9 +166,10 @@ __device__ __forceinline__ void fft_butterfly(cpx<T>* v, int j, const cpx<T>* __
     for (int r = 5; r < R && r < 8; ++r) w[r] = cmul(w[r - 4], w[4]);
     if constexpr (R > 8) w[8] = tw[8 * t];
 #pragma unroll
-    for (int r = 9; r < R; ++r) w[r] = cmul(w[8], w[r - 8]);
-#pragma unroll
-    for (int r = 1; r < R; ++r) v[r] = DIR < 0 ? cmul(v[r], w[r]) : cmulc(v[r], w[r]);
+    for (int r = 1; r < R; ++r) {
+      if (r >= 8) v[r] = DIR < 0 ? cmul(v[r], w[8]) : cmulc(v[r], w[8]);
+      if (r != 8) v[r] = DIR < 0 ? cmul(v[r], w[r & 7]) : cmulc(v[r], w[r & 7]);
+    }
   }
   dft_any<R, DIR>(v);
 }

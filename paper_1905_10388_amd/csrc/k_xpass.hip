@@ -2,6 +2,7 @@
 // dealiasing", Sec. VII "Arithmetic operators"): per dealiased row, packed
 // complex-to-real transforms of the grid fields, the products, and packed
 // real-to-complex transforms truncated to the stored modes (2-D and 3-D).
+#include "fft.h"
 #include "xform.h"
 
 namespace stau {
@@ -32,19 +33,18 @@ namespace stau {
 //              (w_x, w_y), (wz, -)
 template <int DIM>
 __device__ __forceinline__ void pair_src(int k, int& fa, int& da, int& fb, int& db) {
+  // (a nibble per pair, so that a pair picked at run time costs shifts)
+  auto pick = [k](unsigned t) { return (int)((t >> (4 * k)) & 15u); };
   if constexpr (DIM == 2) {
-    constexpr int A[4] = {0, 2, 0, 1}, DA[4] = {0, 1, 1, 1}, B[4] = {1, 3, 4, 5};
-    fa = A[k];
-    da = DA[k];
-    fb = B[k];
+    fa = pick(0x1020);
+    da = pick(0x1110);
+    fb = pick(0x5431);
     db = 0;
   } else {
-    constexpr int A[8] = {0, 2, 4, 0, 7, 8, 2, 11}, DA[8] = {0, 0, 0, 1, 0, 0, 1, 0};
-    constexpr int B[8] = {1, 3, 5, 6, 1, 9, 10, -1}, DB[8] = {0, 1, 0, 0, 1, 0, 0, 0};
-    fa = A[k];
-    da = DA[k];
-    fb = B[k];
-    db = DB[k];
+    fa = pick(0xb2870420);
+    da = pick(0x01001000);
+    fb = k == 7 ? -1 : pick(0x0a916531);
+    db = pick(0x00010010);
   }
 }
 
@@ -426,7 +426,7 @@ __global__ void __launch_bounds__(NT) xrow3_kernel(XformArgs a,
   }
   scatter(!upper);
   __syncthreads();
-  fft_lds_c<LC, +1, MAXBF, T, true, true>(buf, L, 4, twl, tid, NT);
+  fft_lds_c<LC, +1, MAXBF, T, true, LC == 384>(buf, L, 4, twl, tid, NT);
 #pragma unroll
   for (int q = 0; q < PTS; ++q) {
     const int i = tid + q * NT;
@@ -442,7 +442,7 @@ __global__ void __launch_bounds__(NT) xrow3_kernel(XformArgs a,
   __syncthreads();
   scatter(upper);
   __syncthreads();
-  fft_lds_c<LC, +1, MAXBF, T, true, true>(buf, L, 4, twl, tid, NT);
+  fft_lds_c<LC, +1, MAXBF, T, true, LC == 384>(buf, L, 4, twl, tid, NT);
 #pragma unroll
   for (int q = 0; q < PTS; ++q) {
     const int i = tid + q * NT;
@@ -464,7 +464,7 @@ __global__ void __launch_bounds__(NT) xrow3_kernel(XformArgs a,
     }
   }
   __syncthreads();
-  fft_lds_c<LC, -1, MAXBF, T, true, true>(buf, L, 2, twl, tid, NT);
+  fft_lds_c<LC, -1, MAXBF, T, true, LC == 384>(buf, L, 2, twl, tid, NT);
   const T invL = (T)1 / (T)L;
   const T hf = (T)0.5;
   for (int k = tid; k < Px; k += NT) {
@@ -482,31 +482,396 @@ __global__ void __launch_bounds__(NT) xrow3_kernel(XformArgs a,
   }
 }
 
-template <int DIM, int NT, int PTS, int MAXBF, typename T>
+// ---------------------------------------------------------------------------
+// The FP64 x pass at compile-time row lengths L = 3 Nx / 2, from registers to
+// registers: NR rows per block, PT = the last radix, L / PT threads per row, NB2
+// pairs at a time.  The forward transforms run the backward stages in reverse:
+//   * first backward stage, radix R0 = 3 Q: butterfly j takes the entries
+//     j + r W (W = L / R0).  Those of the middle third are the padding, known to
+//     be zero; those of the upper third are the conjugate-symmetric partners of
+//     the lower third's entries of butterfly W - j, so a thread that does both
+//     butterflies reads every entry of the half spectra once;
+//   * last backward stage: a thread owns the grid points j + r L / PT, r < PT, of its
+//     row for every pair, forms the products there and starts the forward
+//     transforms, whose first radix is PT too, from them;
+//   * last forward stage: butterflies j and W - j again hold each entry and its
+//     partner, so the two real fields of a sequence separate in registers; the
+//     dropped third is never formed.
+// Between two stages a sequence goes through LDS once (L = 384: 4 accesses per
+// element), where the in-place transforms of xrow2_kernel and xrow3_kernel have
+// two per pass and two at each end (8 to 10).  Those kernels were bound by LDS
+// and FP64 arithmetic about equally (L = 384: LDS busy for 57 % of the time,
+// arithmetic for 52 %; the memory's share 60 %); the small launches by their
+// chains of passes and, with lengths known at run time only, integer divisions.
+// The stages between the ends are spread over the block by (row, pair,
+// butterfly).  FP32 keeps the in-place kernels (see ypass_fft_kernel).
+// 2-D: two blocks per row, blockIdx.y = 0 forms N_b and N_u, 1 forms N_w.
+// ---------------------------------------------------------------------------
+// the radices of a row length, backward order
+template <int... R>
+struct XPlan {
+  static constexpr int n = sizeof...(R), r[n] = {R...}, L = (R * ...), PT = r[n - 1];
+};
+
+// sequence length in LDS: at radix 12 one entry of padding per 12 (the first
+// stage's writes are R0 entries apart)
+template <typename PL>
+constexpr int xseq() { return PL::r[0] == 12 ? PL::L / 12 * 13 : PL::L; }
+
+template <int DIM, typename PL, int NR, int NB2, int WPE>
+__global__ void __launch_bounds__((NR * (PL::L / PL::PT) + 63) / 64 * 64) __attribute__((amdgpu_waves_per_eu(WPE)))
+    xrow_fft_kernel(XformArgs a, const double2* __restrict__ G, double2* __restrict__ H, int rows) {
+  extern __shared__ double2 smem[];
+  using T = double;
+  using cT = cpx<T>;
+  constexpr int L = PL::L, PT = PL::PT;
+  constexpr int TR = L / PT, R0 = PL::r[0], Q = R0 / 3, W = L / R0, U = W / 2, Pa = L / 3, Px = Pa + 1;
+  constexpr int LS = xseq<PL>(), NST = PL::n, NT = (NR * TR + 63) / 64 * 64;
+  const int tid = threadIdx.x, row = tid / TR, tj = tid - row * TR;
+  const int r0 = blockIdx.x * NR, nrow = rows - r0 < NR ? rows - r0 : NR;
+  const bool on = row < nrow;
+  const size_t R = (size_t)a.M * (DIM == 3 ? a.Ngy : 1);
+  cT* buf = (cT*)smem;  // [row][sequence][LS]
+  const cT* tw = (const cT*)a.twx;
+  // LDS places: backward padded by R0 = 12; forward the low three bits of the
+  // index exchanged with the next three (the first stage writes PT apart)
+  auto atb = [](int i) { return R0 == 12 ? i + i / 12 : i; };
+  auto atf = [](int i) { return i ^ ((i >> 3) & 7); };
+  // (by value: a choice between two elements of register arrays by reference
+  // would put both arrays into scratch memory)
+  auto sel = [](bool c, cT x, cT y) { return mk<T>(c ? x.x : y.x, c ? x.y : y.y); };
+
+  // stages 1 .. NST - 2 of the backward (DIR +1) or forward transform of `count`
+  // (a constant) sequences per row: items (row, sequence, butterfly) over the block
+  auto middle = [&](auto dirc, auto cntc) __attribute__((always_inline)) {
+    constexpr int DIR = decltype(dirc)::value, NC = decltype(cntc)::value;
+    static_for_stage<1, NST - 1>([&](auto sc) {
+      constexpr int S = decltype(sc)::value;
+      constexpr int RS = DIR > 0 ? PL::r[S] : PL::r[NST - 1 - S], WS = L / RS;
+      constexpr int NS = [] {
+        int p = 1;
+        for (int q = 0; q < S; ++q) p *= DIR > 0 ? PL::r[q] : PL::r[NST - 1 - q];
+        return p;
+      }();
+      constexpr int IT = NR * NC * WS, NB = (IT + NT - 1) / NT;
+      cT v[NB][RS];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const int it = tid + b * NT, sq = it / WS, j = it - sq * WS;
+        const cT* B = buf + ((sq / NC) * NB2 + sq % NC) * LS;
+        if (IT % NT == 0 || it < IT) {
+#pragma unroll
+          for (int q = 0; q < RS; ++q) v[b][q] = B[DIR > 0 ? atb(j + q * WS) : atf(j + q * WS)];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const int it = tid + b * NT, sq = it / WS, j = it - sq * WS;
+        cT* B = buf + ((sq / NC) * NB2 + sq % NC) * LS;
+        if (IT % NT == 0 || it < IT) {
+          fft_butterfly<L, RS, NS, DIR, T>(v[b], j, tw);
+          const int o = (j / NS) * NS * RS + j % NS;
+#pragma unroll
+          for (int q = 0; q < RS; ++q) B[DIR > 0 ? atb(o + q * NS) : atf(o + q * NS)] = v[b][q];
+        }
+      }
+      __syncthreads();
+    });
+  };
+
+  // backward transforms of NC pairs, pair i being pk(i); take(i, v): the PT grid
+  // points of pair i, real and imaginary parts the pair's two fields
+  auto backward = [&](auto cntc, auto&& pk, auto&& take) __attribute__((always_inline)) {
+    constexpr int NC = decltype(cntc)::value;
+    constexpr int IT = NR * NC * U, NB = (IT + NT - 1) / NT;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int it = tid + b * NT, sq = it / U, t = it - sq * U, rw = sq / NC, p = sq % NC;
+      if (rw >= nrow) continue;
+      const int j1 = t, j2 = t ? W - t : U, r = r0 + rw;
+      cT* B = buf + (rw * NB2 + p) * LS;
+      int fa, da, fb, db;
+      pair_src<DIM>(pk(p), fa, da, fb, db);
+      const double2* Ga = G + ((size_t)fa * R + r) * Px;
+      const double2* Gb = G + ((size_t)(fb < 0 ? fa : fb) * R + r) * Px;
+      cT a1[Q], a2[Q], b1[Q], b2[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        a1[q] = ldv<T>(Ga + j1 + q * W);
+        a2[q] = ldv<T>(Ga + j2 + q * W);
+        b1[q] = b2[q] = mk<T>(0, 0);
+        if (fb >= 0) {
+          b1[q] = ldv<T>(Gb + j1 + q * W);
+          b2[q] = ldv<T>(Gb + j2 + q * W);
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        if (da) {
+          a1[q] = ikx<T>(a, j1 + q * W, a1[q]);
+          a2[q] = ikx<T>(a, j2 + q * W, a2[q]);
+        }
+        if (db) {
+          b1[q] = ikx<T>(a, j1 + q * W, b1[q]);
+          b2[q] = ikx<T>(a, j2 + q * W, b2[q]);
+        }
+      }
+      if (t == 0) a1[0].y = b1[0].y = 0;  // k = 0: real
+      cT v[R0];
+      // entries of butterfly j1: the lower third from (a1, b1), the upper third
+      // the partners of the lower one's entries of j2 (j1 = 0: its own)
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        v[q] = mk<T>(a1[q].x - b1[q].y, a1[q].y + b1[q].x);
+        v[Q + q] = mk<T>(0, 0);
+        const cT c2 = mk<T>(a2[q].x + b2[q].y, -a2[q].y + b2[q].x);
+        cT n1 = mk<T>(0, 0);  // (j1 = 0: k = (q + 1) W, padding for q = Q - 1)
+        if constexpr (Q > 1) {
+          if (q + 1 < Q) n1 = mk<T>(a1[(q + 1) % Q].x + b1[(q + 1) % Q].y, -a1[(q + 1) % Q].y + b1[(q + 1) % Q].x);
+        }
+        v[R0 - 1 - q] = sel(t, c2, n1);
+      }
+      dft_any<R0, +1>(v);
+#pragma unroll
+      for (int q = 0; q < R0; ++q) B[atb(j1 * R0 + q)] = v[q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        v[q] = mk<T>(a2[q].x - b2[q].y, a2[q].y + b2[q].x);
+        v[Q + q] = mk<T>(0, 0);
+        const cT c1 = mk<T>(a1[q].x + b1[q].y, -a1[q].y + b1[q].x), c2 = mk<T>(a2[q].x + b2[q].y, -a2[q].y + b2[q].x);
+        v[R0 - 1 - q] = sel(t, c1, c2);
+      }
+      dft_any<R0, +1>(v);
+#pragma unroll
+      for (int q = 0; q < R0; ++q) B[atb(j2 * R0 + q)] = v[q];
+    }
+    __syncthreads();
+    middle(std::integral_constant<int, +1>{}, cntc);
+    if (on) {
+      static_for_stage<0, NC>([&](auto pc) {
+        constexpr int p = decltype(pc)::value;
+        const cT* B = buf + (row * NB2 + p) * LS;
+        cT v[PT];
+#pragma unroll
+        for (int q = 0; q < PT; ++q) v[q] = B[atb(tj + q * TR)];
+        fft_butterfly<L, PT, L / PT, +1, T>(v, tj, tw);
+        take(pc, v);
+      });
+    }
+    __syncthreads();
+  };
+
+  const T sc = (T)0.5 / (T)L;
+  // forward transforms of NC sequences: give(i, v) supplies the PT grid points of
+  // sequence i, ea(i) and eb(i) are its two output fields (eb < 0: one)
+  auto forward = [&](auto cntc, auto&& give, auto&& ea, auto&& eb) __attribute__((always_inline)) {
+    constexpr int NC = decltype(cntc)::value;
+    if (on) {
+      static_for_stage<0, NC>([&](auto pc) {
+        constexpr int p = decltype(pc)::value;
+        cT* B = buf + (row * NB2 + p) * LS;
+        cT v[PT];
+        give(pc, v);
+        dft_any<PT, -1>(v);
+#pragma unroll
+        for (int q = 0; q < PT; ++q) B[atf(tj * PT + q)] = v[q];
+      });
+    }
+    __syncthreads();
+    middle(std::integral_constant<int, -1>{}, cntc);
+    constexpr int IT = NR * NC * U, NB = (IT + NT - 1) / NT;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int it = tid + b * NT, sq = it / U, t = it - sq * U, rw = sq / NC, p = sq % NC;
+      if (rw >= nrow) continue;
+      const int j1 = t, j2 = t ? W - t : U, r = r0 + rw;
+      const cT* B = buf + (rw * NB2 + p) * LS;
+      cT v1[R0], v2[R0];
+#pragma unroll
+      for (int q = 0; q < R0; ++q) {
+        v1[q] = B[atf(j1 + q * W)];
+        v2[q] = B[atf(j2 + q * W)];
+      }
+      fft_butterfly<L, R0, W, -1, T>(v1, j1, tw);
+      fft_butterfly<L, R0, W, -1, T>(v2, j2, tw);
+      const int fa = ea(p), fb = eb(p);
+      double2* Ha = H + ((size_t)fa * R + r) * Px;
+      double2* Hb = H + ((size_t)(fb < 0 ? fa : fb) * R + r) * Px;
+      auto put = [&](int k, cT z, cT m) {
+        stv<T>(Ha + k, mk<T>(sc * (z.x + m.x), sc * (z.y - m.y)));
+        if (fb >= 0) stv<T>(Hb + k, mk<T>(sc * (z.y + m.y), -sc * (z.x - m.x)));
+      };
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        // partner L - k of k = j + q W
+        put(j1 + q * W, v1[q], sel(t, v2[R0 - 1 - q], v1[q ? R0 - q : 0]));
+        put(j2 + q * W, v2[q], sel(t, v1[R0 - 1 - q], v2[R0 - 1 - q]));
+      }
+      if (t == 0) {  // Nyquist slot
+        stv<T>(Ha + Pa, mk<T>(0, 0));
+        if (fb >= 0) stv<T>(Hb + Pa, mk<T>(0, 0));
+      }
+    }
+    __syncthreads();
+  };
+
+  using One = std::integral_constant<int, 1>;
+  using Two = std::integral_constant<int, 2>;
+  if constexpr (DIM == 2) {
+    T u[PT], w[PT], nb[PT], nu[PT], nw[PT];
+    auto take = [&](int pk, const cT* v) __attribute__((always_inline)) {  // pk a constant
+#pragma unroll
+      for (int q = 0; q < PT; ++q) {
+        if (pk == 0) {
+          u[q] = v[q].x;
+          w[q] = v[q].y;
+        } else {
+          const T n = -(u[q] * v[q].x + w[q] * v[q].y);
+          if (pk == 1) nb[q] = n;
+          if (pk == 2) nu[q] = n;
+          if (pk == 3) nw[q] = n;
+        }
+      }
+    };
+    auto run1 = [&](auto kc) __attribute__((always_inline)) {
+      constexpr int K = decltype(kc)::value;
+      backward(One{}, [](int) { return K; }, [&](auto, const cT* v) { take(K, v); });
+    };
+    auto run2 = [&](auto k0c, auto k1c) __attribute__((always_inline)) {
+      constexpr int K0 = decltype(k0c)::value, K1 = decltype(k1c)::value;
+      if constexpr (NB2 >= 2) {
+        backward(Two{}, [](int p) { return p ? K1 : K0; },
+                 [&](auto pc, const cT* v) { take(decltype(pc)::value ? K1 : K0, v); });
+      } else {
+        run1(k0c);
+        run1(k1c);
+      }
+    };
+    auto giveA = [&](auto, cT* v) {
+#pragma unroll
+      for (int q = 0; q < PT; ++q) v[q] = mk<T>(nb[q], nu[q]);
+    };
+    auto giveB = [&](auto, cT* v) {
+#pragma unroll
+      for (int q = 0; q < PT; ++q) v[q] = mk<T>(nw[q], (T)0);
+    };
+    using K0 = std::integral_constant<int, 0>;
+    using K3 = std::integral_constant<int, 3>;
+    if (blockIdx.y == 0) {
+      run2(K0{}, One{});
+      run1(Two{});
+      forward(One{}, giveA, [](int) { return 0; }, [](int) { return 1; });
+    } else {
+      run2(K0{}, K3{});
+      forward(One{}, giveB, [](int) { return 2; }, [](int) { return -1; });
+    }
+  } else {
+    T u[PT], v_[PT], w[PT], nb[PT], nu[PT], nv[PT], nw[PT];
+    static_for_stage<0, 8 / NB2>([&](auto kc) {
+      constexpr int K = decltype(kc)::value * NB2;
+      backward(std::integral_constant<int, NB2>{}, [](int p) { return K + p; }, [&](auto pc, const cT* v) {
+        constexpr int kk = K + decltype(pc)::value;
+#pragma unroll
+        for (int q = 0; q < PT; ++q) {
+          const T x = v[q].x, y = v[q].y;
+          if (kk == 0) { u[q] = x; v_[q] = y; }
+          if (kk == 1) { w[q] = x; nb[q] = -(u[q] * y); }
+          if (kk == 2) nb[q] -= v_[q] * x + w[q] * y;
+          if (kk == 3) nu[q] = -(u[q] * x + v_[q] * y);
+          if (kk == 4) { nu[q] -= w[q] * x; nv[q] = -(u[q] * y); }
+          if (kk == 5) nv[q] -= v_[q] * x + w[q] * y;
+          if (kk == 6) nw[q] = -(u[q] * x + v_[q] * y);
+          if (kk == 7) nw[q] -= w[q] * x;
+        }
+      });
+    });
+    forward(Two{}, [&](auto pc, cT* v) {
+#pragma unroll
+      for (int q = 0; q < PT; ++q) v[q] = decltype(pc)::value ? mk<T>(nv[q], nw[q]) : mk<T>(nb[q], nu[q]);
+    }, [](int p) { return 2 * p; }, [](int p) { return 2 * p + 1; });
+  }
+}
+
+template <int DIM, typename PL, int NR, int NB2, int WPE = 2>
+static hipError_t launch_xfft(const XformArgs& a, const void* G, void* H, hipStream_t st) {
+  static_assert(DIM == 2 || NB2 >= 2, "the forward transforms run two at a time in 3-D");
+  constexpr size_t lds = (size_t)NR * NB2 * xseq<PL>() * sizeof(double2);
+  constexpr int NT = (NR * (PL::L / PL::PT) + 63) / 64 * 64;
+  const int rows = a.M * (DIM == 2 ? 1 : a.Ngy);
+  auto fn = xrow_fft_kernel<DIM, PL, NR, NB2, WPE>;
+  allow_lds((const void*)fn, lds);
+  hipLaunchKernelGGL(fn, dim3((rows + NR - 1) / NR, DIM == 2 ? 2 : 1), dim3(NT), lds, st, a, (const double2*)G,
+                     (double2*)H, rows);
+  return hipGetLastError();
+}
+
+// Radices, rows per block and pairs at a time, the fastest of those measured
+// (us, one launch after another; in brackets the in-place kernels):
+//   3-D     24 x 576 rows        4.3 (7.9)      24 x 36864   22 (142)
+//           48 x 2304            6.4 (19)       48 x 9216    13 (55)
+//           96 x 9216            25 (62)       192 x 4608    27 (48)   192 x 36864  177 (296)
+//          384 x 9216          102 (139)       384 x 73728  734 (881)
+//          768 x 2304           57 (109)       768 x 18432  402 (774)
+//   2-D     24 x 24 rows        4.2 (6.7)       48 x 192     4.7 (8.4)  96 x 48       5.1 (8.5)
+//          192 x 48             5.6 (9.4)      384 x 192     6.9 (13)  768 x 192     8.7 (14)
+//         1536 x 384             17 (24)      3072 x 96       14 (30) 6144 x 96       24 (37)
+// Radix 12 loses to 3 or 6 (6-16-4 against 12-8-4 at 384 x 73728: 734, 962), one
+// block per 2-D row to two even where two are more than the units (384 x 768 rows:
+// 9.8 against 9.3 us).
+template <int DIM>
+static hipError_t launch_xfft_L(const XformArgs& a, const void* G, void* H, hipStream_t st, bool& done) {
+  done = true;
+  if constexpr (DIM == 2) {
+    switch (a.L) {
+      case 24: return launch_xfft<2, XPlan<6, 4>, 1, 2>(a, G, H, st);
+      case 48: return launch_xfft<2, XPlan<3, 4, 4>, 1, 2>(a, G, H, st);
+      case 96: return launch_xfft<2, XPlan<3, 8, 4>, 1, 2>(a, G, H, st);
+      case 192: return launch_xfft<2, XPlan<3, 8, 8>, 1, 2>(a, G, H, st);
+      case 384: return launch_xfft<2, XPlan<6, 8, 8>, 1, 2>(a, G, H, st);
+      case 768: return launch_xfft<2, XPlan<6, 16, 8>, 1, 2>(a, G, H, st);
+      case 1536: return launch_xfft<2, XPlan<3, 8, 8, 8>, 1, 2>(a, G, H, st);
+      case 3072: return launch_xfft<2, XPlan<6, 8, 8, 8>, 1, 2>(a, G, H, st);
+      // (two sequences of 6144 points exceed a unit's LDS; 768 threads leave 168 registers)
+      case 6144: return launch_xfft<2, XPlan<6, 16, 8, 8>, 1, 1, 3>(a, G, H, st);
+    }
+  } else {
+    // few rows: all eight pairs at once, four rows per block
+    const bool few = a.M * a.Ngy < 4096;
+    switch (a.L) {
+      case 24:
+        return few ? launch_xfft<3, XPlan<6, 4>, 4, 8>(a, G, H, st) : launch_xfft<3, XPlan<6, 4>, 10, 2>(a, G, H, st);
+      case 48:
+        return few ? launch_xfft<3, XPlan<12, 4>, 4, 8>(a, G, H, st)
+                   : launch_xfft<3, XPlan<12, 4>, 10, 4>(a, G, H, st);
+      case 96: return launch_xfft<3, XPlan<6, 4, 4>, 2, 4>(a, G, H, st);
+      case 192: return launch_xfft<3, XPlan<6, 8, 4>, 2, 4>(a, G, H, st);
+      case 384: return launch_xfft<3, XPlan<6, 16, 4>, 1, 4>(a, G, H, st);
+      case 768: return launch_xfft<3, XPlan<6, 16, 8>, 1, 2>(a, G, H, st);
+    }
+  }
+  done = false;
+  return hipSuccess;
+}
+
+template <int DIM, int NT, int PTS, int MAXBF, typename T, int LC = 0>
 static hipError_t launch_xrow_t(const XformArgs& a, const void* G, void* H, hipStream_t st) {
   using S2 = typename V2<T>::type;
   const int rows = a.M * (DIM == 2 ? 1 : a.Ngy);
   const bool twl = (size_t)a.L * sizeof(S2) <= 32768;
   const size_t lds = (size_t)a.L * sizeof(S2) * (twl ? 2 : 1);
   // 2-D rows fewer than compute units (FP32: fewer than twice as many): two
-  // blocks per row.  (Measured at 1536 x 384 points: FP32 27.8 -> 21.6 us
-  // split; FP64 37.8 -> 41.3 us, so FP64 keeps one block per row there.)
+  // blocks per row.  (Measured at 1536 x 384 points: FP32 27.8 -> 21.6 us.)
   int dev = 0, cus = 0;
   const bool split = DIM == 2 && hipGetDevice(&dev) == hipSuccess &&
                      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
                      rows < (sizeof(T) == 4 ? 2 * cus : cus);
   const dim3 grid(rows, split ? 2 : 1);
   // 2-D: pairs two at a time when two sequences and the twiddles fit 80 KB
-  if constexpr (DIM == 2) {
+  if constexpr (DIM == 2 && (LC == 0 || 3 * LC * sizeof(S2) <= 80 * 1024)) {
     const size_t lds2 = (size_t)3 * a.L * sizeof(S2);
     if (lds2 <= 80 * 1024) {
-      // 1536-point rows (Nx = 1024) with the length fixed at compile time
-      constexpr bool k1536 = NT * PTS >= 1536 && NT * PTS < 3072;
-      auto fn = split ? xrow2_kernel<NT, PTS, 2 * MAXBF, T, true> : xrow2_kernel<NT, PTS, 2 * MAXBF, T, false>;
-      if constexpr (k1536) {
-        if (a.L == 1536)
-          fn = split ? xrow2_kernel<NT, PTS, 2 * MAXBF, T, true, 1536> : xrow2_kernel<NT, PTS, 2 * MAXBF, T, false, 1536>;
-      }
+      auto fn = split ? xrow2_kernel<NT, PTS, 2 * MAXBF, T, true, LC> : xrow2_kernel<NT, PTS, 2 * MAXBF, T, false, LC>;
       allow_lds((const void*)fn, lds2);
       hipLaunchKernelGGL(fn, grid, dim3(NT), lds2, st, a, (const S2*)G, (S2*)H);
       return hipGetLastError();
@@ -516,41 +881,24 @@ static hipError_t launch_xrow_t(const XformArgs& a, const void* G, void* H, hipS
   // points), when four sequences and the twiddles fit 64 KB
   if constexpr (DIM == 3 && NT <= 512) {
     constexpr int PTS3 = (PTS + 1) / 2;
-    const bool c384 = a.L == 384 && 2 * NT * PTS3 >= 384;
-    const size_t lds3 = ((size_t)4 * a.L + (c384 ? 64 : a.L)) * sizeof(S2);
+    const size_t lds3 = ((size_t)4 * a.L + (LC == 384 ? 64 : a.L)) * sizeof(S2);
     if (lds3 <= 64 * 1024 && a.L <= 2 * NT * PTS3 && a.Pa <= NT) {
-      // the 256 x 256 workload's 384-point rows with their length fixed
-      // (and 64 twiddles in LDS: 25 KB per block, six blocks per unit)
-      auto fn = c384 ? xrow3_kernel<2 * NT, PTS3, 2 * MAXBF, T, 384>
-                     : xrow3_kernel<2 * NT, PTS3, 2 * MAXBF, T, 0>;
+      auto fn = xrow3_kernel<2 * NT, PTS3, 2 * MAXBF, T, LC>;
       allow_lds((const void*)fn, lds3);
       hipLaunchKernelGGL(fn, grid, dim3(2 * NT), lds3, st, a, (const S2*)G, (S2*)H);
       return hipGetLastError();
     }
   }
-  // 2-D 6144-point rows (Nx = 4096) with the length fixed at compile time
-  if constexpr (DIM == 2 && NT * PTS >= 6144) {
-    if (a.L == 6144 && !twl) {
-      auto fn = split ? xrow_kernel<DIM, NT, PTS, MAXBF, false, T, true, 6144>
-                      : xrow_kernel<DIM, NT, PTS, MAXBF, false, T, false, 6144>;
-      allow_lds((const void*)fn, lds);
-      hipLaunchKernelGGL(fn, grid, dim3(NT), lds, st, a, (const S2*)G, (S2*)H);
-      return hipGetLastError();
-    }
-    if (a.L == 6144 && twl) {
-      auto fn = split ? xrow_kernel<DIM, NT, PTS, MAXBF, true, T, true, 6144>
-                      : xrow_kernel<DIM, NT, PTS, MAXBF, true, T, false, 6144>;
+  if constexpr (LC == 0 || LC * sizeof(S2) <= 32768) {
+    if (twl) {
+      auto fn = split ? xrow_kernel<DIM, NT, PTS, MAXBF, true, T, true, LC> : xrow_kernel<DIM, NT, PTS, MAXBF, true, T, false, LC>;
       allow_lds((const void*)fn, lds);
       hipLaunchKernelGGL(fn, grid, dim3(NT), lds, st, a, (const S2*)G, (S2*)H);
       return hipGetLastError();
     }
   }
-  if (twl) {
-    auto fn = split ? xrow_kernel<DIM, NT, PTS, MAXBF, true, T, true> : xrow_kernel<DIM, NT, PTS, MAXBF, true, T, false>;
-    allow_lds((const void*)fn, lds);
-    hipLaunchKernelGGL(fn, grid, dim3(NT), lds, st, a, (const S2*)G, (S2*)H);
-  } else {
-    auto fn = split ? xrow_kernel<DIM, NT, PTS, MAXBF, false, T, true> : xrow_kernel<DIM, NT, PTS, MAXBF, false, T, false>;
+  if constexpr (LC == 0 || LC * sizeof(S2) > 32768) {
+    auto fn = split ? xrow_kernel<DIM, NT, PTS, MAXBF, false, T, true, LC> : xrow_kernel<DIM, NT, PTS, MAXBF, false, T, false, LC>;
     allow_lds((const void*)fn, lds);
     hipLaunchKernelGGL(fn, grid, dim3(NT), lds, st, a, (const S2*)G, (S2*)H);
   }
@@ -560,14 +908,33 @@ static hipError_t launch_xrow_t(const XformArgs& a, const void* G, void* H, hipS
 template <int DIM, typename T>
 static hipError_t launch_xrow_T(const XformArgs& a, const void* G, void* H, hipStream_t st) {
   const int L = a.L;
+  if constexpr (sizeof(T) == 8) {
+    bool done;
+    const hipError_t e = launch_xfft_L<DIM>(a, G, H, st, done);
+    if (done) return e;
+  } else {
+    // the in-place kernels with the length fixed (the bits of the general ones)
+    switch (L) {
+      case 24: return launch_xrow_t<DIM, 64, 1, 1, T, 24>(a, G, H, st);
+      case 48: return launch_xrow_t<DIM, 64, 1, 1, T, 48>(a, G, H, st);
+      case 96: return launch_xrow_t<DIM, 64, 2, 1, T, 96>(a, G, H, st);
+      case 192: return launch_xrow_t<DIM, 64, 3, 1, T, 192>(a, G, H, st);
+      case 384: return launch_xrow_t<DIM, 128, 3, 1, T, 384>(a, G, H, st);
+      case 768: return launch_xrow_t<DIM, 256, 3, 1, T, 768>(a, G, H, st);
+    }
+    if constexpr (DIM == 2) switch (L) {
+      case 1536: return launch_xrow_t<DIM, 512, 3, 1, T, 1536>(a, G, H, st);
+      case 3072: return launch_xrow_t<DIM, 1024, 3, 1, T, 3072>(a, G, H, st);
+      case 6144: return launch_xrow_t<DIM, 1024, 6, 2, T, 6144>(a, G, H, st);
+    }
+  }
+  // Nx = 4 and 8, and 3-D rows of more than 512 points
   if (L <= 64) return launch_xrow_t<DIM, 64, 1, 1, T>(a, G, H, st);
-  if (L <= 128) return launch_xrow_t<DIM, 64, 2, 1, T>(a, G, H, st);
-  if (L <= 192) return launch_xrow_t<DIM, 64, 3, 1, T>(a, G, H, st);
-  if (L <= 384) return launch_xrow_t<DIM, 128, 3, 1, T>(a, G, H, st);
-  if (L <= 768) return launch_xrow_t<DIM, 256, 3, 1, T>(a, G, H, st);
-  if (L <= 1536) return launch_xrow_t<DIM, 512, 3, 1, T>(a, G, H, st);
-  if (L <= 3072) return launch_xrow_t<DIM, 1024, 3, 1, T>(a, G, H, st);
-  if (L <= 6144) return launch_xrow_t<DIM, 1024, 6, 2, T>(a, G, H, st);
+  if constexpr (DIM == 3) {
+    if (L <= 1536) return launch_xrow_t<DIM, 512, 3, 1, T>(a, G, H, st);
+    if (L <= 3072) return launch_xrow_t<DIM, 1024, 3, 1, T>(a, G, H, st);
+    if (L <= 6144) return launch_xrow_t<DIM, 1024, 6, 2, T>(a, G, H, st);
+  }
   return hipErrorInvalidValue;
 }
 

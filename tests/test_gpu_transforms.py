@@ -1,6 +1,7 @@
-"""The transforms at compile-time padded lengths (24 to 768 points in y), at
-their tile edges: fewer columns than a tile, exactly one tile, several, and
-a length next to the general kernels' (12 points).
+"""The transforms at compile-time padded lengths (24 to 768 points in y, 24 to
+6144 in x, 24 to 768 in 3-D), at their tile edges: fewer columns than a tile,
+exactly one tile, several; few rows and many with a partial last block; and
+lengths next to them that the general kernels take (12 points; 1536 in 3-D).
 
 * The explicit term (both y directions with the y derivatives formed on the
   way) and a padded grid transform there and back, FP64, against the oracle,
@@ -27,6 +28,9 @@ from paper_1905_10388_amd import RBSolver  # noqa: E402
 # dim, Nx, Ny, Nz
 Y_SHAPES = [(3, 8, 8, 4), (3, 4, 16, 8), (3, 32, 16, 4), (3, 64, 8, 4), (3, 64, 32, 4), (3, 8, 64, 8),
             (3, 4, 128, 4), (3, 32, 128, 4), (3, 4, 256, 4), (3, 16, 256, 4), (3, 4, 512, 4), (3, 16, 512, 4)]
+X_SHAPES = [(2, Nx, 1, 8) for Nx in (8, 16, 32, 64, 128, 256, 512, 1024, 2048, 4096)] + [
+    (3, 16, 4, 4), (3, 16, 64, 64), (3, 32, 4, 8), (3, 32, 64, 64), (3, 64, 8, 4), (3, 128, 4, 4), (3, 256, 4, 4),
+    (3, 512, 4, 4), (3, 1024, 4, 4)]
 
 
 def _np(t):
@@ -51,7 +55,7 @@ def _state(o, seed):
     return X
 
 
-@pytest.mark.parametrize("shape", Y_SHAPES, ids=lambda s: "-".join(str(v) for v in s))
+@pytest.mark.parametrize("shape", Y_SHAPES + X_SHAPES, ids=lambda s: "-".join(str(v) for v in s))
 def test_explicit_term_and_grid_round_trip(shape):
     o, g = _pair(shape)
     X = _state(o, 41)
@@ -63,7 +67,7 @@ def test_explicit_term_and_grid_round_trip(shape):
     assert rel_err(_np(Xg)[..., o.vi["w"], :], o.from_grid(ref)) < 1e-13
 
 
-@pytest.mark.parametrize("shape", Y_SHAPES, ids=lambda s: "-".join(str(v) for v in s))
+@pytest.mark.parametrize("shape", Y_SHAPES + X_SHAPES, ids=lambda s: "-".join(str(v) for v in s))
 def test_mixed_explicit_term(shape):
     o, g = _pair(shape, precision="mixed", dct="fft")
     X = 1e3 * _state(o, 42)

@@ -95,9 +95,9 @@ typedef struct stau_pencils stau_pencils;
  *          kinetic-energy and initial-state adjoints run in FP64 in either
  *          mode.
  * device   HIP device ordinal.
- * dct_method  Chebyshev z transforms of the step: STAU_DCT_AUTO (matrix
- *          products for Nz <= 64, FFT otherwise), STAU_DCT_FFT (DCT through
- *          one complex FFT per column), STAU_DCT_MATMUL (dense products on the
+ * dct_method  Chebyshev z transforms of the step: STAU_DCT_AUTO and
+ *          STAU_DCT_FFT (DCT through one complex FFT per column; the mixed
+ *          step's AUTO below), STAU_DCT_MATMUL (dense products on the
  *          FP64 matrix cores; Nz a multiple of 32 in [32, 256], else
  *          STAU_EUNSUPPORTED).  In the mixed-precision step the products
  *          run as split-BF16 matrix-core products with FP32 accumulation

@@ -80,55 +80,18 @@ __device__ __forceinline__ void dft_any(cpx<T>* v) {
   else if constexpr (R > 1) dftR<R, DIR>(v);
 }
 
-// Radix of stage s (1 beyond the last), for lengths 2^a and 3 2^a up to 6144:
-// stages of at most 16 points, the factor 3 first.
-constexpr int fft_radix(int M, int s) {
-  int r = 1;
-  for (int q = 0; q <= s; ++q) {
-    const bool three = M % 3 == 0;
-    const int p2 = three ? M / 3 : M;
-    if (M == 1) r = 1;
-    else if (three) {
-      // 3, 6 or 12, so that the rest is stages of radix 16, 8 and (24) 4
-      if (p2 == 1) r = 3;
-      else if (p2 == 2) r = 6;
-      else if (p2 == 4) r = 12;
-      else if (p2 == 8) r = 6;                  // 24 = 6 x 4
-      else if (p2 == 16) r = 6;                 // 48 = 6 x 8
-      else if (p2 == 32) r = 12;                // 96 = 12 x 8
-      else if (p2 == 64) r = 12;                // 192 = 12 x 16
-      else if (p2 == 128) r = 6;                // 384 = 6 x 8 x 8
-      else if (p2 == 256) r = 12;               // 768 = 12 x 8 x 8
-      else if (p2 == 512) r = 12;               // 1536 = 12 x 16 x 8
-      else if (p2 == 1024) r = 12;              // 3072 = 12 x 16 x 16
-      else r = 6;                               // 6144 = 6 x 16 x 8 x 8
-    } else if (p2 <= 8) r = p2;
-    else if (p2 == 16) r = q == 0 ? 4 : 16;
-    else if (p2 == 32) r = 4;
-    else if (p2 == 64) r = 8;
-    else if (p2 == 128) r = 16;
-    else if (p2 == 256) r = 16;
-    else if (p2 == 512) r = 8;
-    else r = 16;
-    M /= r;
+// The radices of a transform's stages, in order.
+template <int... R>
+struct FftPlan {
+  static constexpr int n = sizeof...(R), r[n] = {R...}, L = (R * ...), PT = r[n - 1];
+  static constexpr int ns(int s) { return s == 0 ? 1 : ns(s - 1) * r[s - 1]; }
+  // most butterflies of a stage
+  static constexpr int width() {
+    int w = 0;
+    for (int s = 0; s < n; ++s) w = L / r[s] > w ? L / r[s] : w;
+    return w;
   }
-  return r;
-}
-constexpr int fft_ns(int M, int s) {
-  return s == 0 ? 1 : fft_ns(M, s - 1) * fft_radix(M, s - 1);
-}
-constexpr int fft_stages(int M) {
-  int s = 0;
-  while (fft_ns(M, s) < M) ++s;
-  return s;
-}
-// most butterflies of a stage
-constexpr int fft_width(int M) {
-  int w = 0;
-  for (int s = 0; s < fft_stages(M); ++s)
-    if (M / fft_radix(M, s) > w) w = M / fft_radix(M, s);
-  return w;
-}
+};
 
 template <int I, int N, typename F>
 __device__ __forceinline__ void static_for_stage(F&& f) {
@@ -174,18 +137,20 @@ __device__ __forceinline__ void fft_butterfly(cpx<T>* v, int j, const cpx<T>* __
   dft_any<R, DIR>(v);
 }
 
-// B transforms of length M by NT threads.  load(b, s, j, v) fills the first
+// B transforms of the plan PL by NT threads.  load(b, s, j, v) fills the first
 // stage's inputs (b counts the thread's butterflies), store(s, j, v) takes the
-// last stage's outputs (elements j + r M / R of sequence s).  at(s, i): LDS position of element i.  SF0, SFL: sequences
-// fastest over the threads in the first and last stage (the stages between
-// follow the last).
-template <int M, int DIR, int B, int NT, bool SF0, bool SFL, typename T, typename LD, typename ST, typename AT>
+// last stage's outputs (elements j + r M / R of sequence s); without LAST the
+// last stage is left to the caller, its inputs in LDS.  at(s, i): LDS place of
+// element i.  SF0, SFL: sequences fastest over the threads in the first and last
+// stage (the stages between follow the last).
+template <typename PL, int DIR, int B, int NT, bool SF0, bool SFL, bool LAST, typename T, typename LD, typename ST,
+          typename AT>
 __device__ __forceinline__ void fft_block(cpx<T>* buf, const cpx<T>* __restrict__ tw, int tid, LD&& load, ST&& store,
                                           AT&& at) {
-  constexpr int NST = fft_stages(M);
-  static_for_stage<0, NST>([&](auto sc) {
+  constexpr int M = PL::L, NST = PL::n;
+  static_for_stage<0, LAST ? NST : NST - 1>([&](auto sc) {
     constexpr int S = decltype(sc)::value;
-    constexpr int R = fft_radix(M, S), NS = fft_ns(M, S), W = M / R, NB = (B * W + NT - 1) / NT;
+    constexpr int R = PL::r[S], NS = PL::ns(S), W = M / R, NB = (B * W + NT - 1) / NT;
     constexpr bool SF = S == 0 ? SF0 : SFL, whole = NB * NT == B * W;
     cpx<T> v[NB][R];
     if (S > 0) __syncthreads();
@@ -221,6 +186,7 @@ __device__ __forceinline__ void fft_block(cpx<T>* buf, const cpx<T>* __restrict_
       }
     }
   });
+  if constexpr (!LAST) __syncthreads();
 }
 
 }  // namespace stau

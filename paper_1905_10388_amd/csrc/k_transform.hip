@@ -257,6 +257,202 @@ __global__ void __launch_bounds__(kZThreads) zf_kernel(XformArgs a,
 }
 
 // ---------------------------------------------------------------------------
+// The FP64 z transforms at the dealiased lengths M = 3 N / 2 (24 to 768),
+// registers to registers (fft_block), TP pencils per block, a pencil's row in
+// LDS padded by one entry so that both orders of access spread over the banks.
+//   zb: threads along n read the state (first radix 3 Q: the lower third of a
+//     butterfly's points has the entry n only, the upper third M - n only), the
+//     last stage stores with the pencils fastest.
+//   zf: the first stage loads with the pencils fastest; in the last stage a
+//     thread does the butterflies j and W - j, which hold V_n and V_{M-n}; the
+//     epilogue (right-hand side and history) runs along n.
+// Bound by the memory where the launch fills the chip (256x256x128: zb 272 us
+// for 1.35 GB, zf 429 us for 2.0 GB; the in-place transforms with LDS passes of
+// their own for scatter, reflection and reordering took 310 and 482), by the
+// latency of load, stages and store where it does not.  Against the FP64
+// matrix products that N <= 64 used before (us): 64x32 zb 7.3 -> 6.4, zf 10.5
+// -> 6.7; 4096x64 23 -> 11, 23 -> 14; 128x32x64 27 -> 12.6, 25 -> 16; 32x32x32
+// 9.4 -> 7.1, 11.8 -> 7.7.
+// ---------------------------------------------------------------------------
+template <typename PL, int TP, int NT>
+__global__ void __launch_bounds__(NT) zb_fft_kernel(XformArgs a, FieldList fl, const double2* __restrict__ X,
+                                                    double2* __restrict__ G) {
+  extern __shared__ double2 smem[];
+  constexpr int M = PL::L, N = M / 3 * 2, R0 = PL::r[0], W = M / R0, RL = PL::PT;
+  static_assert(R0 % 3 == 0, "thirds of the first stage");
+  const int S = fl.src_S ? fl.src_S : a.S, f = blockIdx.y, p0 = blockIdx.x * TP;
+  const int var = fl.var[f], der = fl.deriv[f], tid = threadIdx.x;
+  const PencilBase pb = pencil_base(a, p0);
+  // T_n(z_j) weights: (2 - delta_n0) / M of the adjoint use, halves of the cosine sum
+  const double w0 = fl.wmode ? 1.0 / (double)M : 1.0, wn = fl.wmode ? 1.0 / (double)M : 0.5;
+  auto load = [&](int, int s, int j, cd* v) {
+    const bool act = active_at(a, pb, s);
+    const double2* col = X + ((size_t)(p0 + s) * S + var) * N;
+    double2 x[R0], y[R0];
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      // stored entries of a point n and of its mirror M - n: the lower third has
+      // n only, the upper third M - n only
+      const int n = j + r * W;
+      x[r] = y[r] = make_double2(0.0, 0.0);
+      if (act && 3 * r < 2 * R0) x[r] = col[n];
+      if (act && 3 * r >= R0 && M - n < N) y[r] = col[M - n];
+    }
+    double kk = 0.0;
+    if (der == 1) kk = kx_at(a, pb, s);
+    if (der == 2) kk = ky_at(a, pb, s);
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      const int n = j + r * W;
+      // (T_n on the ascending grid: (-1)^n; M is even, so the mirror has n's sign)
+      const double sg = (n & 1) ? -1.0 : 1.0;
+      const double sx = sg * (r == 0 && j == 0 ? w0 : wn), sy = sg * wn;
+      cd yn = mk(sx * x[r].x, sx * x[r].y), ym = mk(sy * y[r].x, sy * y[r].y);
+      if (der) {
+        yn = mk(-kk * yn.y, kk * yn.x);
+        ym = mk(-kk * ym.y, kk * ym.x);
+      }
+      v[r] = cmul(ld2(a.dctz + n), mk(yn.x + ym.y, yn.y - ym.x));  // e^{i pi n / 2M} (Y_n - i Y_{M-n})
+    }
+  };
+  auto store = [&](int s, int j, cd* v) {
+    if (p0 + s >= a.P) return;
+    double2* g = G + (size_t)f * M * a.P + p0 + s;
+#pragma unroll
+    for (int r = 0; r < RL; ++r) {
+      const int i = j + r * (M / RL), jz = 2 * i < M ? 2 * i : 2 * (M - 1 - i) + 1;
+      st2(g + (size_t)jz * a.P, v[r]);
+    }
+  };
+  fft_block<PL, +1, TP, NT, false, true, true, double>((cd*)smem, (const cd*)a.twz, tid, load, store,
+                                                        [](int s, int i) { return s * (M + 1) + i; });
+}
+
+template <typename PL, int TP, int NT, bool RK>
+__global__ void __launch_bounds__(NT) zf_fft_kernel(XformArgs a, const double2* __restrict__ H,
+                                                    double2* __restrict__ out, RhsArgs r) {
+  extern __shared__ double2 smem[];
+  constexpr int M = PL::L, N = M / 3 * 2, R0 = PL::r[0], W0 = M / R0, RL = PL::PT, W = M / RL, U = W / 2;
+  static_assert(RL % 3 == 0 && TP * U <= NT, "thirds of the last stage, one pair of butterflies per thread");
+  cd* buf = (cd*)smem;
+  const int ne = a.ne, e = blockIdx.y, p0 = blockIdx.x * TP, tid = threadIdx.x;
+  const PencilBase pb = pencil_base(a, p0);
+  if (r.mode >= 1 && a.dim == 2 && blockIdx.x == 0) {
+    // pencils beyond the grid (2-D, p >= Pa): inactive, zero right-hand side
+    // (and history)
+    for (int p = a.Pa; p < a.P; ++p)
+      for (int nn = tid; nn < N; nn += NT) {
+        const size_t o = ((size_t)p * ne + e) * N + nn;
+        out[o] = make_double2(0.0, 0.0);
+        if (r.mode == 1) {
+          const size_t ho = (((size_t)p * 2) * ne + e) * N + nn;
+          r.hist_cur[ho] = make_double2(0.0, 0.0);
+          r.hist_cur[ho + (size_t)ne * N] = make_double2(0.0, 0.0);
+        }
+      }
+  }
+  auto load = [&](int, int s, int j, cd* v) {
+    const double2* h = H + (size_t)e * M * a.P + p0 + s;
+    const bool in = p0 + s < a.P;
+#pragma unroll
+    for (int q = 0; q < R0; ++q) {
+      const int i = j + q * W0, jz = 2 * i < M ? 2 * i : 2 * (M - 1 - i) + 1;
+      v[q] = in ? ld2(h + (size_t)jz * a.P) : mk(0.0, 0.0);
+    }
+  };
+  auto at = [](int s, int i) { return s * (M + 1) + i; };
+  fft_block<PL, -1, TP, NT, true, true, false, double>(buf, (const cd*)a.twz, tid, load,
+                                                        [](int, int, cd*) {}, at);
+  // last stage: butterflies j and W - j hold V_n and V_{M-n}
+  const int s0 = tid % TP, t = tid / TP;
+  const bool own = t < U;
+  const int j1 = t, j2 = t ? W - t : U;
+  cd v1[RL], v2[RL];
+  if (own) {
+#pragma unroll
+    for (int q = 0; q < RL; ++q) {
+      v1[q] = buf[at(s0, j1 + q * W)];
+      v2[q] = buf[at(s0, j2 + q * W)];
+    }
+  }
+  __syncthreads();
+  if (own) {
+    fft_butterfly<M, RL, W, -1, double>(v1, j1, (const cd*)a.twz);
+    fft_butterfly<M, RL, W, -1, double>(v2, j2, (const cd*)a.twz);
+    auto put = [&](int n, cd V, cd Vm) {
+      const cd w = conj(ld2(a.dctz + n));
+      const cd P = cmul(w, V), Q = cmul(w, conj(Vm));
+      double sc = (n == 0 ? 0.5 : 1.0) / (double)M;
+      if (n & 1) sc = -sc;
+      buf[at(s0, n)] = mk(sc * (P.x + Q.x), sc * (P.y - Q.y));
+    };
+    auto sel = [](bool c, cd x, cd y) { return mk(c ? x.x : y.x, c ? x.y : y.y); };
+#pragma unroll
+    for (int q = 0; 3 * q < 2 * RL; ++q) {
+      put(j1 + q * W, v1[q], sel(t, v2[RL - 1 - q], v1[q ? RL - q : 0]));
+      put(j2 + q * W, v2[q], sel(t, v1[RL - 1 - q], v2[RL - 1 - q]));
+    }
+  }
+  __syncthreads();
+  // epilogue in groups of up to four points per thread: a group's state and
+  // history loads are issued together
+  constexpr int IT = TP * N / NT, GE = IT % 4 == 0 ? 4 : IT % 3 == 0 ? 3 : IT % 2 == 0 ? 2 : 1;
+  static_assert(IT * NT == TP * N, "whole epilogue");
+#pragma unroll
+  for (int g0 = 0; g0 < IT; g0 += GE) {
+    double2 x0[GE], x2[GE], fo[GE], mo[GE];
+    RkRow rv[RK ? GE : 1];
+#pragma unroll
+    for (int u = 0; u < GE; ++u) {
+      const int idx = tid + (g0 + u) * NT, s = idx / N, nn = idx - s * N, p = p0 + s;
+      x0[u] = x2[u] = fo[u] = mo[u] = make_double2(0.0, 0.0);
+      if (r.mode >= 1 && active_at(a, pb, s) && nn <= N - 2) {
+        const double2* xc = r.Xprev + ((size_t)p * a.S + (e + 1)) * N;
+        x0[u] = xc[nn];
+        if (nn + 2 < N) x2[u] = xc[nn + 2];
+        if constexpr (RK) rk_load(r.rk, ((size_t)p * ne + e) * N + nn, rv[u]);
+        if (r.mode == 1 && r.has_hist) {
+          const size_t ho = (((size_t)p * 2) * ne + e) * N + nn;
+          fo[u] = r.hist_old[ho];
+          mo[u] = r.hist_old[ho + (size_t)ne * N];
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < GE; ++u) {
+      const int idx = tid + (g0 + u) * NT, s = idx / N, nn = idx - s * N, p = p0 + s;
+      if (p >= a.P) continue;
+      const size_t o = ((size_t)p * ne + e) * N + nn;
+      if (r.mode == 0) {
+        st2(out + o, buf[at(s, nn)]);
+        continue;
+      }
+      cd Ft = mk(0.0, 0.0), MX = mk(0.0, 0.0), B = mk(0.0, 0.0);
+      if (active_at(a, pb, s) && nn <= N - 2) {
+        const double cnn = nn == 0 ? 1.0 : 0.5;
+        Ft = scale(buf[at(s, nn)], cnn);
+        if (nn + 2 < N) Ft = Ft - scale(buf[at(s, nn + 2)], 0.5);
+        MX = scale(mk(x0[u].x, x0[u].y), cnn) - scale(mk(x2[u].x, x2[u].y), 0.5);
+        if constexpr (RK) {
+          rk_finish(r.rk, o, rv[u], make_double2(Ft.x, Ft.y), make_double2(MX.x, MX.y), out);
+          continue;
+        }
+        B = scale(Ft, r.c1) - scale(MX, r.a1);
+        if (r.has_hist) B = B + scale(mk(fo[u].x, fo[u].y), r.c2) - scale(mk(mo[u].x, mo[u].y), r.a2);
+      }
+      if constexpr (RK) {  // inactive pencil or row N - 1
+        st2(out + o, B);
+        continue;
+      }
+      const size_t ho = (((size_t)p * 2) * ne + e) * N + nn;
+      st2(r.hist_cur + ho, Ft);
+      st2(r.hist_cur + ho + (size_t)ne * N, MX);
+      st2(out + o, B);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // y pass (3-D): complex transforms along y of TK consecutive kx columns per
 // block, one (field, z level) per (blockIdx.z, blockIdx.y).  Stored y slots
 // iy hold the signed wavenumbers 0..Ny/2-1, [Nyquist, held zero],
@@ -397,12 +593,12 @@ __global__ void __launch_bounds__(256) ypass_kernel(XformArgs a,
 // bits): registers to registers the compiler contracts products into sums in
 // other places, which FP32 results show (4e-6 of the history).
 constexpr int ytile(int NG) { return NG <= 96 ? 16 : NG == 192 ? 8 : 4; }
-constexpr int ythreads(int NG, int TK) {
-  const int n = (TK * fft_width(NG) + 63) / 64 * 64;
+constexpr int ythreads(int width, int TK) {
+  const int n = (TK * width + 63) / 64 * 64;
   return n > 256 ? 256 : n;
 }
 
-template <int DIR, int NG, int TK = ytile(NG), int NT = ythreads(NG, TK)>
+template <int DIR, typename PL, int TK = ytile(PL::L), int NT = ythreads(PL::width(), TK)>
 __global__ void __launch_bounds__(NT) ypass_fft_kernel(XformArgs a, const double2* __restrict__ In,
                                                        double2* __restrict__ Out, double ys, YMap ym) {
   extern __shared__ double2 smem[];
@@ -422,8 +618,8 @@ __global__ void __launch_bounds__(NT) ypass_fft_kernel(XformArgs a, const double
       f = lin / nby;
     }
   }
-  constexpr int Ny = NG / 3 * 2, half = NG / 3;
-  constexpr int R0 = fft_radix(NG, 0), RL = fft_radix(NG, fft_stages(NG) - 1);
+  constexpr int NG = PL::L, Ny = NG / 3 * 2, half = NG / 3;
+  constexpr int R0 = PL::r[0], RL = PL::PT;
   const int Px = a.Px, M = a.M, k0 = bx * TK, tid = threadIdx.x;
   constexpr size_t inRows = DIR > 0 ? Ny : NG, outRows = DIR > 0 ? NG : Ny;
   const int fin = ym.n ? ym.src[f] : f;
@@ -472,7 +668,7 @@ __global__ void __launch_bounds__(NT) ypass_fft_kernel(XformArgs a, const double
       for (int iy = tid; iy < Ny; iy += NT) stv<T>(dst + (size_t)iy * Px + (a.Pa - k0), mk<T>(0, 0));
   }
   const cT* tw = (const cT*)a.twy;
-  fft_block<NG, DIR, TK, NT, true, true, T>(buf, tw, tid, load, store, [](int s, int i) { return i * TK + s; });
+  fft_block<PL, DIR, TK, NT, true, true, true, T>(buf, tw, tid, load, store, [](int s, int i) { return i * TK + s; });
 }
 
 // ---------------------------------------------------------------------------
@@ -635,8 +831,41 @@ __global__ void ke_sum_kernel(const double2* __restrict__ c, int N, double* out)
   if (threadIdx.x == 0) *out = red[0];
 }
 
+template <typename PL, int TP, int NT>
+static hipError_t launch_zb_fft(const XformArgs& a, const FieldList& fl, const void* X, void* G, int plaunch,
+                                hipStream_t st) {
+  constexpr size_t lds = (size_t)TP * (PL::L + 1) * sizeof(double2);
+  auto fn = zb_fft_kernel<PL, TP, NT>;
+  allow_lds((const void*)fn, lds);
+  hipLaunchKernelGGL(fn, dim3((plaunch + TP - 1) / TP, fl.nf), dim3(NT), lds, st, a, fl, (const double2*)X,
+                     (double2*)G);
+  return hipGetLastError();
+}
+
 hipError_t launch_zb(const XformArgs& a, const FieldList& fl, const void* X, void* G,
                      hipStream_t st, bool fp32, bool active_only) {
+  if (!fp32 && 2 * a.M == 3 * a.N) {
+    const int plaunch = active_only && a.dim == 2 ? a.Pa : a.P;
+    // half tiles where whole ones leave units with less than two blocks (64x32:
+    // zf 8.8 -> 6.7 us; 512x128: 14 -> 10.5; 1024x256: zb 13.8 -> 12.9, zf 17.3 -> 15.8)
+    const bool few = (plaunch + 7) / 8 * fl.nf < 2 * unit_count();
+    switch (a.M) {
+      case 24: return launch_zb_fft<FftPlan<6, 4>, 8, 64>(a, fl, X, G, plaunch, st);
+      case 48:
+        return few ? launch_zb_fft<FftPlan<6, 8>, 4, 64>(a, fl, X, G, plaunch, st)
+                   : launch_zb_fft<FftPlan<6, 8>, 8, 64>(a, fl, X, G, plaunch, st);
+      case 96:
+        return few ? launch_zb_fft<FftPlan<6, 4, 4>, 4, 128>(a, fl, X, G, plaunch, st)
+                   : launch_zb_fft<FftPlan<6, 4, 4>, 8, 128>(a, fl, X, G, plaunch, st);
+      case 192:
+        return few ? launch_zb_fft<FftPlan<6, 8, 4>, 4, 192>(a, fl, X, G, plaunch, st)
+                   : launch_zb_fft<FftPlan<6, 8, 4>, 8, 256>(a, fl, X, G, plaunch, st);
+      case 384:
+        return few ? launch_zb_fft<FftPlan<6, 8, 8>, 4, 256>(a, fl, X, G, plaunch, st)
+                   : launch_zb_fft<FftPlan<6, 8, 8>, 8, 256>(a, fl, X, G, plaunch, st);
+      case 768: return launch_zb_fft<FftPlan<6, 4, 4, 8>, 4, 256>(a, fl, X, G, plaunch, st);
+    }
+  }
   int TP = z_tile(a.M);
   if (TP * a.M != kZPts) return hipErrorInvalidValue;
   const int plaunch = active_only && a.dim == 2 ? a.Pa : a.P;
@@ -649,30 +878,55 @@ hipError_t launch_zb(const XformArgs& a, const FieldList& fl, const void* X, voi
     allow_lds((const void*)kern, lds);
     hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, a, fl, (const double2*)X, g, TP);
   };
-  // the workloads' dealiased lengths (Nz = 64, 128, 256) with M fixed at compile time
+  // FP32: the workloads' dealiased lengths (Nz = 64, 128, 256) with M fixed at compile time
   auto pick = [&](auto tc, auto g) {
     using TT = typename decltype(tc)::type;
-    if (a.M == 192) {
-      if (dv == 2) go(zb_kernel<3, TT, kZEpt / 2, 192>, g);
-      else go(zb_kernel<3, TT, kZEpt, 192>, g);
-    } else if (a.M == 384) {
-      if (dv == 2) go(zb_kernel<3, TT, kZEpt / 2, 384>, g);
-      else go(zb_kernel<3, TT, kZEpt, 384>, g);
-    } else if (a.M == 96) {
-      if (dv == 2) go(zb_kernel<3, TT, kZEpt / 2, 96>, g);
-      else go(zb_kernel<3, TT, kZEpt, 96>, g);
-    } else {
-      if (dv == 2) go(zb_kernel<3, TT, kZEpt / 2>, g);
-      else go(zb_kernel<3, TT>, g);
+    if constexpr (sizeof(TT) == 4) {
+      if (a.M == 192) return dv == 2 ? go(zb_kernel<3, TT, kZEpt / 2, 192>, g) : go(zb_kernel<3, TT, kZEpt, 192>, g);
+      if (a.M == 384) return dv == 2 ? go(zb_kernel<3, TT, kZEpt / 2, 384>, g) : go(zb_kernel<3, TT, kZEpt, 384>, g);
+      if (a.M == 96) return dv == 2 ? go(zb_kernel<3, TT, kZEpt / 2, 96>, g) : go(zb_kernel<3, TT, kZEpt, 96>, g);
     }
+    if (dv == 2) go(zb_kernel<3, TT, kZEpt / 2>, g);
+    else go(zb_kernel<3, TT>, g);
   };
   if (fp32) pick(std::common_type<float>(), (float2*)G);
   else pick(std::common_type<double>(), (double2*)G);
   return hipGetLastError();
 }
 
+template <typename PL, int TP, int NT>
+static hipError_t launch_zf_fft(const XformArgs& a, const void* H, void* out, const RhsArgs& r, int plaunch,
+                                hipStream_t st) {
+  constexpr size_t lds = (size_t)TP * (PL::L + 1) * sizeof(double2);
+  auto fn = r.mode == 2 ? zf_fft_kernel<PL, TP, NT, true> : zf_fft_kernel<PL, TP, NT, false>;
+  allow_lds((const void*)fn, lds);
+  hipLaunchKernelGGL(fn, dim3((plaunch + TP - 1) / TP, a.ne), dim3(NT), lds, st, a, (const double2*)H, (double2*)out,
+                     r);
+  return hipGetLastError();
+}
+
 hipError_t launch_zf(const XformArgs& a, const void* H, void* out, const RhsArgs& r,
                      hipStream_t st, bool fp32) {
+  if (!fp32 && 2 * a.M == 3 * a.N) {
+    const int plaunch = a.dim == 2 && r.mode >= 1 ? a.Pa : a.P;
+    const bool few = (plaunch + 7) / 8 * a.ne < 2 * unit_count();  // (as in launch_zb)
+    switch (a.M) {
+      case 24: return launch_zf_fft<FftPlan<4, 6>, 8, 64>(a, H, out, r, plaunch, st);
+      case 48:
+        return few ? launch_zf_fft<FftPlan<8, 6>, 4, 64>(a, H, out, r, plaunch, st)
+                   : launch_zf_fft<FftPlan<8, 6>, 8, 64>(a, H, out, r, plaunch, st);
+      case 96:
+        return few ? launch_zf_fft<FftPlan<4, 4, 6>, 4, 64>(a, H, out, r, plaunch, st)
+                   : launch_zf_fft<FftPlan<4, 4, 6>, 8, 128>(a, H, out, r, plaunch, st);
+      case 192:
+        return few ? launch_zf_fft<FftPlan<4, 8, 6>, 4, 128>(a, H, out, r, plaunch, st)
+                   : launch_zf_fft<FftPlan<4, 8, 6>, 8, 128>(a, H, out, r, plaunch, st);
+      case 384:
+        return few ? launch_zf_fft<FftPlan<8, 8, 6>, 4, 256>(a, H, out, r, plaunch, st)
+                   : launch_zf_fft<FftPlan<8, 8, 6>, 8, 256>(a, H, out, r, plaunch, st);
+      case 768: return launch_zf_fft<FftPlan<8, 4, 4, 6>, 4, 256>(a, H, out, r, plaunch, st);
+    }
+  }
   int TP = z_tile(a.M);
   if (TP * a.M != kZPts || TP * a.N > 12 * kZThreads) return hipErrorInvalidValue;
   const int plaunch = (a.dim == 2 && r.mode >= 1) ? a.Pa : a.P;
@@ -689,26 +943,26 @@ hipError_t launch_zf(const XformArgs& a, const void* H, void* out, const RhsArgs
   };
   const float2* h32 = (const float2*)H;
   const double2* h64 = (const double2*)H;
-  // the workloads' (M, N) = (96, 64), (192, 128), (384, 256) fixed at compile
-  // time, with the epilogue's points per thread (TP N / threads: 8 for full
-  // tiles at M = 3N/2, 4 for half tiles); other lengths (the scale-1
+  // FP32: the workloads' (M, N) = (96, 64), (192, 128), (384, 256) fixed at
+  // compile time, with the epilogue's points per thread (TP N / threads: 8 for
+  // full tiles at M = 3N/2, 4 for half tiles); other lengths (the scale-1
   // transforms, M = N) up to 12 and 8
   auto pick = [&](auto tc, auto rk, auto h) {
     using TT = typename decltype(tc)::type;
     constexpr bool RKv = decltype(rk)::value;
-    if (a.M == 192 && a.N == 128) {
-      if (dv == 2) go(zf_kernel<3, 4, TT, RKv, kZEpt / 2, 192, 128>, h);
-      else go(zf_kernel<3, 8, TT, RKv, kZEpt, 192, 128>, h);
-    } else if (a.M == 384 && a.N == 256) {
-      if (dv == 2) go(zf_kernel<3, 4, TT, RKv, kZEpt / 2, 384, 256>, h);
-      else go(zf_kernel<3, 8, TT, RKv, kZEpt, 384, 256>, h);
-    } else if (a.M == 96 && a.N == 64) {
-      if (dv == 2) go(zf_kernel<3, 4, TT, RKv, kZEpt / 2, 96, 64>, h);
-      else go(zf_kernel<3, 8, TT, RKv, kZEpt, 96, 64>, h);
-    } else {
-      if (dv == 2) go(zf_kernel<3, 8, TT, RKv, kZEpt / 2>, h);
-      else go(zf_kernel<3, 12, TT, RKv>, h);
+    if constexpr (sizeof(TT) == 4) {
+      if (a.M == 192 && a.N == 128)
+        return dv == 2 ? go(zf_kernel<3, 4, TT, RKv, kZEpt / 2, 192, 128>, h)
+                       : go(zf_kernel<3, 8, TT, RKv, kZEpt, 192, 128>, h);
+      if (a.M == 384 && a.N == 256)
+        return dv == 2 ? go(zf_kernel<3, 4, TT, RKv, kZEpt / 2, 384, 256>, h)
+                       : go(zf_kernel<3, 8, TT, RKv, kZEpt, 384, 256>, h);
+      if (a.M == 96 && a.N == 64)
+        return dv == 2 ? go(zf_kernel<3, 4, TT, RKv, kZEpt / 2, 96, 64>, h)
+                       : go(zf_kernel<3, 8, TT, RKv, kZEpt, 96, 64>, h);
     }
+    if (dv == 2) go(zf_kernel<3, 8, TT, RKv, kZEpt / 2>, h);
+    else go(zf_kernel<3, 12, TT, RKv>, h);
   };
   using tf = std::common_type<float>;
   using td = std::common_type<double>;
@@ -723,9 +977,10 @@ hipError_t launch_zf(const XformArgs& a, const void* H, void* out, const RhsArgs
 }
 
 
-template <int NG>
+template <typename PL>
 static hipError_t launch_ypass_ct(const XformArgs& a, int dir, int nf, const void* In, void* Out, hipStream_t st,
                                   bool fp32, double ys, const YMap& ym) {
+  constexpr int NG = PL::L;
   if (fp32) {
     // tiles of 32 (24 points), 16 or 3072 / NG columns
     constexpr int TK = NG == 24 ? 32 : NG <= 192 ? 16 : 3072 / NG, PB = TK * NG, BF = (PB + 1023) / 1024;
@@ -733,8 +988,8 @@ static hipError_t launch_ypass_ct(const XformArgs& a, int dir, int nf, const voi
     hipLaunchKernelGGL(fn, dim3((a.Pa + TK - 1) / TK, a.M, nf), dim3(256), PB * sizeof(float2), st, a,
                        (const float2*)In, (float2*)Out, TK, ys, ym);
   } else {
-    constexpr int TK = ytile(NG), NT = ythreads(NG, TK);
-    auto fn = dir > 0 ? ypass_fft_kernel<+1, NG> : ypass_fft_kernel<-1, NG>;
+    constexpr int TK = ytile(NG), NT = ythreads(PL::width(), TK);
+    auto fn = dir > 0 ? ypass_fft_kernel<+1, PL> : ypass_fft_kernel<-1, PL>;
     hipLaunchKernelGGL(fn, dim3((a.Pa + TK - 1) / TK, a.M, nf), dim3(NT), TK * NG * sizeof(double2), st, a,
                        (const double2*)In, (double2*)Out, ys, ym);
   }
@@ -748,9 +1003,9 @@ hipError_t launch_ypass(const XformArgs& a, int dir, int nf, const void* In, voi
   // the dealiased lengths of Ny = 16 .. 512; the other lengths (the scale-1
   // transforms and the shortest and longest) at run time
   if (2 * a.Ngy == 3 * a.Ny) {
-#define STAU_Y(NG) \
-  case NG: return launch_ypass_ct<NG>(a, dir, nf, In, Out, st, fp32, ys, ym);
-    switch (a.Ngy) { STAU_Y(24) STAU_Y(48) STAU_Y(96) STAU_Y(192) STAU_Y(384) STAU_Y(768) }
+#define STAU_Y(...) \
+  case FftPlan<__VA_ARGS__>::L: return launch_ypass_ct<FftPlan<__VA_ARGS__>>(a, dir, nf, In, Out, st, fp32, ys, ym);
+    switch (a.Ngy) { STAU_Y(6, 4) STAU_Y(6, 8) STAU_Y(12, 8) STAU_Y(12, 16) STAU_Y(6, 8, 8) STAU_Y(12, 8, 8) }
 #undef STAU_Y
   }
   const int TK = a.Ngy >= 3072 ? 1 : 3072 / a.Ngy;

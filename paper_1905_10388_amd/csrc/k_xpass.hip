@@ -507,12 +507,6 @@ __global__ void __launch_bounds__(NT) xrow3_kernel(XformArgs a,
 // butterfly).  FP32 keeps the in-place kernels (see ypass_fft_kernel).
 // 2-D: two blocks per row, blockIdx.y = 0 forms N_b and N_u, 1 forms N_w.
 // ---------------------------------------------------------------------------
-// the radices of a row length, backward order
-template <int... R>
-struct XPlan {
-  static constexpr int n = sizeof...(R), r[n] = {R...}, L = (R * ...), PT = r[n - 1];
-};
-
 // sequence length in LDS: at radix 12 one entry of padding per 12 (the first
 // stage's writes are R0 entries apart)
 template <typename PL>
@@ -824,30 +818,30 @@ static hipError_t launch_xfft_L(const XformArgs& a, const void* G, void* H, hipS
   done = true;
   if constexpr (DIM == 2) {
     switch (a.L) {
-      case 24: return launch_xfft<2, XPlan<6, 4>, 1, 2>(a, G, H, st);
-      case 48: return launch_xfft<2, XPlan<3, 4, 4>, 1, 2>(a, G, H, st);
-      case 96: return launch_xfft<2, XPlan<3, 8, 4>, 1, 2>(a, G, H, st);
-      case 192: return launch_xfft<2, XPlan<3, 8, 8>, 1, 2>(a, G, H, st);
-      case 384: return launch_xfft<2, XPlan<6, 8, 8>, 1, 2>(a, G, H, st);
-      case 768: return launch_xfft<2, XPlan<6, 16, 8>, 1, 2>(a, G, H, st);
-      case 1536: return launch_xfft<2, XPlan<3, 8, 8, 8>, 1, 2>(a, G, H, st);
-      case 3072: return launch_xfft<2, XPlan<6, 8, 8, 8>, 1, 2>(a, G, H, st);
+      case 24: return launch_xfft<2, FftPlan<6, 4>, 1, 2>(a, G, H, st);
+      case 48: return launch_xfft<2, FftPlan<3, 4, 4>, 1, 2>(a, G, H, st);
+      case 96: return launch_xfft<2, FftPlan<3, 8, 4>, 1, 2>(a, G, H, st);
+      case 192: return launch_xfft<2, FftPlan<3, 8, 8>, 1, 2>(a, G, H, st);
+      case 384: return launch_xfft<2, FftPlan<6, 8, 8>, 1, 2>(a, G, H, st);
+      case 768: return launch_xfft<2, FftPlan<6, 16, 8>, 1, 2>(a, G, H, st);
+      case 1536: return launch_xfft<2, FftPlan<3, 8, 8, 8>, 1, 2>(a, G, H, st);
+      case 3072: return launch_xfft<2, FftPlan<6, 8, 8, 8>, 1, 2>(a, G, H, st);
       // (two sequences of 6144 points exceed a unit's LDS; 768 threads leave 168 registers)
-      case 6144: return launch_xfft<2, XPlan<6, 16, 8, 8>, 1, 1, 3>(a, G, H, st);
+      case 6144: return launch_xfft<2, FftPlan<6, 16, 8, 8>, 1, 1, 3>(a, G, H, st);
     }
   } else {
     // few rows: all eight pairs at once, four rows per block
     const bool few = a.M * a.Ngy < 4096;
     switch (a.L) {
       case 24:
-        return few ? launch_xfft<3, XPlan<6, 4>, 4, 8>(a, G, H, st) : launch_xfft<3, XPlan<6, 4>, 10, 2>(a, G, H, st);
+        return few ? launch_xfft<3, FftPlan<6, 4>, 4, 8>(a, G, H, st) : launch_xfft<3, FftPlan<6, 4>, 10, 2>(a, G, H, st);
       case 48:
-        return few ? launch_xfft<3, XPlan<12, 4>, 4, 8>(a, G, H, st)
-                   : launch_xfft<3, XPlan<12, 4>, 10, 4>(a, G, H, st);
-      case 96: return launch_xfft<3, XPlan<6, 4, 4>, 2, 4>(a, G, H, st);
-      case 192: return launch_xfft<3, XPlan<6, 8, 4>, 2, 4>(a, G, H, st);
-      case 384: return launch_xfft<3, XPlan<6, 16, 4>, 1, 4>(a, G, H, st);
-      case 768: return launch_xfft<3, XPlan<6, 16, 8>, 1, 2>(a, G, H, st);
+        return few ? launch_xfft<3, FftPlan<12, 4>, 4, 8>(a, G, H, st)
+                   : launch_xfft<3, FftPlan<12, 4>, 10, 4>(a, G, H, st);
+      case 96: return launch_xfft<3, FftPlan<6, 4, 4>, 2, 4>(a, G, H, st);
+      case 192: return launch_xfft<3, FftPlan<6, 8, 4>, 2, 4>(a, G, H, st);
+      case 384: return launch_xfft<3, FftPlan<6, 16, 4>, 1, 4>(a, G, H, st);
+      case 768: return launch_xfft<3, FftPlan<6, 16, 8>, 1, 2>(a, G, H, st);
     }
   }
   done = false;

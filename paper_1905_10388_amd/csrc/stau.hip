@@ -396,8 +396,8 @@ int stau_create_domain(const stau_domain_desc* desc, stau_domain** out) {
   if ((rc = upload(t, &dom->dctz1))) goto bad;
   fft_table(d.Nx, t);
   if ((rc = upload(t, &dom->twx1))) goto bad;
-  dom->mm = mm_supported((int)d.Nz) &&
-            (d.dct_method == STAU_DCT_MATMUL || (d.dct_method == STAU_DCT_AUTO && d.Nz <= 64));
+  // FP64: auto is the FFT at every length (4096x64: 11 / 14 us against 23 / 23 for the products)
+  dom->mm = mm_supported((int)d.Nz) && d.dct_method == STAU_DCT_MATMUL;
   // split-BF16 products for the mixed step: auto takes them for Nz = 64 only
   // (4096x64: 13.8 / 14.4 us against 27.8 / 27.3 for the FP32 FFT); at
   // Nz = 128, 256 the FP32 FFT with half-size tiles is faster (1024x256:

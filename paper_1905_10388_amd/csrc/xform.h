@@ -136,6 +136,15 @@ inline void allow_lds(const void* fn, size_t bytes) {
   if (bytes > 65536) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
+// compute units of the current device
+inline int unit_count() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return 256;
+  return cus;
+}
+
 inline int z_tile(int M) { return M >= 3072 ? 1 : 3072 / M; }
 inline int x_threads(int L) {
   int nt = (L + 5) / 6;

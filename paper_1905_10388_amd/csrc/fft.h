@@ -80,11 +80,21 @@ __device__ __forceinline__ void dft_any(cpx<T>* v) {
   else if constexpr (R > 1) dftR<R, DIR>(v);
 }
 
+template <int... R>
+struct FftPlan;
+template <>
+struct FftPlan<> {};
+template <typename P, int... R>
+struct FftReverse {
+  using type = P;
+};
+
 // The radices of a transform's stages, in order.
 template <int... R>
 struct FftPlan {
   static constexpr int n = sizeof...(R), r[n] = {R...}, L = (R * ...), PT = r[n - 1];
   static constexpr int ns(int s) { return s == 0 ? 1 : ns(s - 1) * r[s - 1]; }
+  using reverse = typename FftReverse<FftPlan<>, R...>::type;
   // most butterflies of a stage
   static constexpr int width() {
     int w = 0;
@@ -92,6 +102,9 @@ struct FftPlan {
     return w;
   }
 };
+
+template <int... D, int R0, int... R>
+struct FftReverse<FftPlan<D...>, R0, R...> : FftReverse<FftPlan<R0, D...>, R...> {};
 
 template <int I, int N, typename F>
 __device__ __forceinline__ void static_for_stage(F&& f) {

@@ -2,7 +2,7 @@
 // manipulation": a field's grid data and its coefficient data; Sec. IV
 // "Scaled transforms & dealiasing": grids at scale 1 or 3/2), and their
 // adjoints.  The z and y stages reuse the step's transform kernels; this file
-// holds the x stage on the caller's grid layout and the gathers.
+// holds the x stage on the caller's grid layout.
 //
 // Grid layout (real float64): g[f][ix][l][jz] (2-D: g[f][ix][jz]), with
 // ix < Lg = scale Nx, l < scale Ny, jz < Mg = scale Nz on the ascending
@@ -21,14 +21,13 @@
 // One block transforms TZ consecutive z levels of one (field, y level): the
 // grid values of a fixed ix are TZ contiguous doubles, and two real rows are
 // packed into each complex FFT (TZ / 2 sequences of Lg points in LDS).
-#include "common.h"
-#include "kernels.h"
+#include "fft.h"
+#include "xform.h"
 
 namespace stau {
 
 namespace {
 
-using cd = cpx<double>;
 constexpr int kGThreads = 256;
 constexpr int kGMaxBF = 6;          // butterflies per thread per radix-4 pass
 constexpr int kGMaxPoints = 6144;   // (TZ / 2) * Lg complex points per block
@@ -97,17 +96,104 @@ __global__ void __launch_bounds__(kGThreads) xgrid_kernel(XformArgs a, int Lg, i
   }
 }
 
-// F[p][f][n] (nf fields) -> X[p][var_f][n] for every pencil slot
-__global__ void put_vars_kernel(int P, int S, int N, FieldList fl, const double2* __restrict__ F,
-                                double2* __restrict__ X) {
-  const size_t total = (size_t)P * fl.nf * N;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-       i += (size_t)gridDim.x * blockDim.x) {
-    const int n = (int)(i % N);
-    const size_t q = i / N;
-    const int f = (int)(q % fl.nf);
-    const size_t p = q / fl.nf;
-    X[(p * S + fl.var[f]) * N + n] = F[i];
+// A pair of grid values of the caller's array, which is aligned to its doubles only
+struct __attribute__((aligned(8))) GridPair {
+  double x, y;
+};
+
+// The same at the compile-time padded lengths L = 3 Nx / 2, registers to registers
+// (fft_block): NSQ pairs of z levels per block, entries of the half spectra
+// read and written along k, grid values along z.  The synthesis forms the packed
+// spectrum in its first stage's inputs (the middle third is zero); in the last
+// stage of the analysis a thread does the butterflies j and W - j, which hold
+// an entry and its conjugate partner.  Bound by the memory (128x128x64, four
+// fields, 190 MB: synthesis 67 -> 39 us, analysis 75 -> 33 us against
+// xgrid_kernel, whose index divisions and LDS passes took as long again).
+template <typename PL, int NSQ, int NT>
+__global__ void __launch_bounds__(NT) xsynth_kernel(XformArgs a, int Ngy, int Mg, const double2* __restrict__ S,
+                                                    double* __restrict__ g, double s0, double s1) {
+  extern __shared__ double2 smem[];
+  constexpr int L = PL::L, Pa = L / 3, Px = Pa + 1, R0 = PL::r[0], W = L / R0, RL = PL::PT;
+  static_assert(R0 % 3 == 0, "thirds of the first stage");
+  const int jz0 = blockIdx.x * 2 * NSQ, l = blockIdx.y, f = blockIdx.z, tid = threadIdx.x;
+  auto load = [&](int, int s, int j, cd* v) {
+    const int jz = jz0 + 2 * s;
+    const double2* A = S + (((size_t)f * Mg + jz) * Ngy + l) * Px;
+    const double2* B = A + (size_t)Ngy * Px;
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      v[r] = mk(0.0, 0.0);
+      if (3 * r >= R0 && 3 * r < 2 * R0) continue;  // padding
+      const bool up = 3 * r >= R0;
+      const int k = j + r * W, kk = up ? L - k : k;
+      if (jz >= Mg || kk >= Pa) continue;
+      cd Ak = ld2(A + kk), Bk = ld2(B + kk);
+      const double w = kk == 0 ? s0 : s1;
+      Ak = mk(w * Ak.x, kk == 0 ? 0.0 : w * Ak.y);
+      Bk = mk(w * Bk.x, kk == 0 ? 0.0 : w * Bk.y);
+      v[r] = up ? mk(Ak.x + Bk.y, Bk.x - Ak.y) : mk(Ak.x - Bk.y, Ak.y + Bk.x);
+    }
+  };
+  auto store = [&](int s, int j, cd* v) {
+    const int jz = jz0 + 2 * s;
+    if (jz >= Mg) return;
+#pragma unroll
+    for (int r = 0; r < RL; ++r) {
+      const int ix = j + r * (L / RL);
+      *(GridPair*)(g + (((size_t)f * L + ix) * Ngy + l) * Mg + jz) = GridPair{v[r].x, v[r].y};
+    }
+  };
+  fft_block<PL, +1, NSQ, NT, false, true, true, double>((cd*)smem, (const cd*)a.twx, tid, load, store,
+                                                         [](int s, int i) { return s * (L + 1) + i; });
+}
+
+template <typename PL, int NSQ, int NT>
+__global__ void __launch_bounds__(NT) xanal_kernel(XformArgs a, int Ngy, int Mg, const double* __restrict__ g,
+                                                   double2* __restrict__ S, double s0, double s1) {
+  extern __shared__ double2 smem[];
+  constexpr int L = PL::L, Pa = L / 3, Px = Pa + 1, R0 = PL::r[0], RL = PL::PT, W = L / RL, U = W / 2;
+  static_assert(RL % 3 == 0 && NSQ * U <= NT, "thirds of the last stage, one pair of butterflies per thread");
+  cd* buf = (cd*)smem;
+  const int jz0 = blockIdx.x * 2 * NSQ, l = blockIdx.y, f = blockIdx.z, tid = threadIdx.x;
+  auto load = [&](int, int s, int j, cd* v) {
+    const int jz = jz0 + 2 * s;
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      v[r] = mk(0.0, 0.0);
+      if (jz >= Mg) continue;
+      const GridPair q = *(const GridPair*)(g + (((size_t)f * L + j + r * (L / R0)) * Ngy + l) * Mg + jz);
+      v[r] = mk(q.x, q.y);
+    }
+  };
+  auto at = [](int s, int i) { return s * (L + 1) + i; };
+  fft_block<PL, -1, NSQ, NT, true, true, false, double>(buf, (const cd*)a.twx, tid, load, [](int, int, cd*) {}, at);
+  const int s = tid / U, t = tid - s * U, jz = jz0 + 2 * s;
+  if (s >= NSQ || jz >= Mg) return;
+  const int j1 = t, j2 = t ? W - t : U;
+  cd v1[RL], v2[RL];
+#pragma unroll
+  for (int q = 0; q < RL; ++q) {
+    v1[q] = buf[at(s, j1 + q * W)];
+    v2[q] = buf[at(s, j2 + q * W)];
+  }
+  fft_butterfly<L, RL, W, -1, double>(v1, j1, (const cd*)a.twx);
+  fft_butterfly<L, RL, W, -1, double>(v2, j2, (const cd*)a.twx);
+  double2* SA = S + (((size_t)f * Mg + jz) * Ngy + l) * Px;
+  double2* SB = SA + (size_t)Ngy * Px;
+  auto put = [&](int k, cd Z, cd Zm) {  // A_k = (Z_k + conj Z_{-k}) / 2, B_k = (Z_k - conj Z_{-k}) / (2 i)
+    const double w = 0.5 * (k == 0 ? s0 : s1);
+    st2(SA + k, mk(w * (Z.x + Zm.x), w * (Z.y - Zm.y)));
+    st2(SB + k, mk(w * (Z.y + Zm.y), -w * (Z.x - Zm.x)));
+  };
+  auto sel = [](bool c, cd x, cd y) { return mk(c ? x.x : y.x, c ? x.y : y.y); };
+#pragma unroll
+  for (int q = 0; 3 * q < RL; ++q) {
+    put(j1 + q * W, v1[q], sel(t, v2[RL - 1 - q], v1[q ? RL - q : 0]));
+    put(j2 + q * W, v2[q], sel(t, v1[RL - 1 - q], v2[RL - 1 - q]));
+  }
+  if (t == 0) {
+    st2(SA + Pa, mk(0.0, 0.0));
+    st2(SB + Pa, mk(0.0, 0.0));
   }
 }
 
@@ -137,10 +223,42 @@ bool xgrid_supported(int Lg, int Mg) {
   return Mg % 2 == 0 && (TZ / 2) * Lg <= kGMaxPoints;
 }
 
+template <int NSQ, int NT, int... R>
+static hipError_t launch_xgrid_ct(const XformArgs& a, int dir, int nf, int Ngy, int Mg, const void* in, void* out,
+                                  double s0, double s1, hipStream_t st) {
+  using SY = FftPlan<R...>;
+  using AN = typename FftPlan<R...>::reverse;
+  constexpr size_t lds = (size_t)NSQ * (SY::L + 1) * sizeof(double2);
+  const dim3 grid((Mg + 2 * NSQ - 1) / (2 * NSQ), Ngy, nf);
+  if (dir > 0) {
+    auto fn = xsynth_kernel<SY, NSQ, NT>;
+    allow_lds((const void*)fn, lds);
+    hipLaunchKernelGGL(fn, grid, dim3(NT), lds, st, a, Ngy, Mg, (const double2*)in, (double*)out, s0, s1);
+  } else {
+    auto fn = xanal_kernel<AN, NSQ, NT>;
+    allow_lds((const void*)fn, lds);
+    hipLaunchKernelGGL(fn, grid, dim3(NT), lds, st, a, Ngy, Mg, (const double*)in, (double2*)out, s0, s1);
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_xgrid(const XformArgs& a, int dir, int nf, int Lg, int Ngy, int Mg,
                         const double2* tw, const void* in, void* out, double s0, double s1,
                         hipStream_t st) {
   if (!xgrid_supported(Lg, Mg)) return hipErrorInvalidValue;
+  // the dealiased lengths of Nx = 16 .. 4096: up to eight pairs of z levels (128
+  // bytes of a grid row) in 98 KB of LDS; the scale-1 lengths at run time
+  if (Lg == 3 * a.Pa) switch (Lg) {
+    case 24: return launch_xgrid_ct<8, 64, 6, 4>(a, dir, nf, Ngy, Mg, in, out, s0, s1, st);
+    case 48: return launch_xgrid_ct<8, 64, 6, 8>(a, dir, nf, Ngy, Mg, in, out, s0, s1, st);
+    case 96: return launch_xgrid_ct<8, 128, 6, 4, 4>(a, dir, nf, Ngy, Mg, in, out, s0, s1, st);
+    case 192: return launch_xgrid_ct<8, 128, 6, 8, 4>(a, dir, nf, Ngy, Mg, in, out, s0, s1, st);
+    case 384: return launch_xgrid_ct<8, 256, 6, 8, 8>(a, dir, nf, Ngy, Mg, in, out, s0, s1, st);
+    case 768: return launch_xgrid_ct<4, 256, 6, 4, 4, 8>(a, dir, nf, Ngy, Mg, in, out, s0, s1, st);
+    case 1536: return launch_xgrid_ct<2, 256, 6, 4, 8, 8>(a, dir, nf, Ngy, Mg, in, out, s0, s1, st);
+    case 3072: return launch_xgrid_ct<2, 512, 6, 8, 8, 8>(a, dir, nf, Ngy, Mg, in, out, s0, s1, st);
+    case 6144: return launch_xgrid_ct<1, 512, 6, 16, 8, 8>(a, dir, nf, Ngy, Mg, in, out, s0, s1, st);
+  }
   // the largest power of two TZ <= 16 dividing Mg with (TZ / 2) Lg points in LDS
   int TZ = 2;
   while (TZ < 16 && Mg % (2 * TZ) == 0 && TZ * Lg <= kGMaxPoints) TZ *= 2;
@@ -154,13 +272,6 @@ hipError_t launch_xgrid(const XformArgs& a, int dir, int nf, int Lg, int Ngy, in
   else
     hipLaunchKernelGGL(xgrid_kernel<-1>, grid, dim3(kGThreads), lds, st, a, Lg, Ngy, Mg, tw, in, out,
                        s0, s1, TZ);
-  return hipGetLastError();
-}
-
-hipError_t launch_put_vars(int P, int S, int N, const FieldList& fl, const void* F, void* X,
-                           hipStream_t st) {
-  hipLaunchKernelGGL(put_vars_kernel, dim3(grid_blocks((size_t)P * fl.nf * N)), dim3(256), 0, st, P,
-                     S, N, fl, (const double2*)F, (double2*)X);
   return hipGetLastError();
 }
 

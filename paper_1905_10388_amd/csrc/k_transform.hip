@@ -99,7 +99,7 @@ __global__ void __launch_bounds__(kZThreads) zb_kernel(XformArgs a, FieldList fl
 
 // ---------------------------------------------------------------------------
 // Forward z (DCT-II with truncation M -> N): c_n = (2 - d_n0)/M sum_j g_j T_n(z_j).
-// mode 0: F[p][e][n] = c_n.
+// mode 0: F[p][e][n] = c_n (or the state's variable, RhsArgs::S).
 // mode 1: SBDF right-hand side of the evolved-equation U-rows:
 //   F~_n = P^L c (n <= N-2), MX_n = P^L X^{n-1}_e,
 //   B_n = c1 F~_n - a1 MX_n + [c2 F~old_n - a2 MXold_n],
@@ -228,7 +228,7 @@ __global__ void __launch_bounds__(kZThreads) zf_kernel(XformArgs a,
         return mk((double)v.x, (double)v.y);
       };
       if (r.mode == 0) {
-        st2(out + o, cget(nn));
+        st2(out + (r.S ? ((size_t)p * r.S + r.var[e]) * N + nn : o), cget(nn));
         continue;
       }
       cd Ft = mk(0.0, 0.0), MX = mk(0.0, 0.0), B = mk(0.0, 0.0);
@@ -424,7 +424,7 @@ __global__ void __launch_bounds__(NT) zf_fft_kernel(XformArgs a, const double2* 
       if (p >= a.P) continue;
       const size_t o = ((size_t)p * ne + e) * N + nn;
       if (r.mode == 0) {
-        st2(out + o, buf[at(s, nn)]);
+        st2(out + (r.S ? ((size_t)p * r.S + r.var[e]) * N + nn : o), buf[at(s, nn)]);
         continue;
       }
       cd Ft = mk(0.0, 0.0), MX = mk(0.0, 0.0), B = mk(0.0, 0.0);

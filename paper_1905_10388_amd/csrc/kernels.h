@@ -227,6 +227,9 @@ struct RhsArgs {
   double2* hist_cur;     // [P][2][ne][N]
   const double2* hist_old;
   RkArgs rk;
+  // mode 0: output e goes to variable var[e] of the state out[p][S][N] (S = 0: to
+  // out[p][e][N])
+  int S, var[9];
 };
 
 // Right-hand side of Runge-Kutta stage i at one evolved-equation U-row
@@ -360,8 +363,6 @@ bool xgrid_supported(int Lg, int Mg);
 hipError_t launch_xgrid(const XformArgs& a, int dir, int nf, int Lg, int Ngy, int Mg,
                         const double2* tw, const void* in, void* out, double s0, double s1,
                         hipStream_t st);
-hipError_t launch_put_vars(int P, int S, int N, const FieldList& fl, const void* F, void* X,
-                           hipStream_t st);
 hipError_t launch_zero_vars(int P, int S, int N, const FieldList& fl, void* X, hipStream_t st);
 
 // kinetic energy: mean over x of |u|^2/2 per z row, then Chebyshev integral

@@ -1537,17 +1537,17 @@ int stau_grid_to_coeff(stau_pencils* pen, const double* grid, uint32_t vars, dou
   hipStream_t st = (hipStream_t)stream;
   HIP_TRY(hipSetDevice(pen->dom->d.device));
   const bool d3 = xa.dim == 3;
-  // x analysis to spectral rows, (y analysis,) z analysis to F[P][nf][N]
+  // x analysis to spectral rows, (y analysis,) z analysis into the state's variables
   double2* rows = d3 ? pen->G2 : pen->G;
   HIP_TRY(launch_xgrid(xa, -1, fl.nf, Lg, Ngy, Mg, xa.twx, grid, rows, 1.0 / Lg, 1.0 / Lg, st));
   if (d3) HIP_TRY(launch_ypass(xa, -1, fl.nf, pen->G2, pen->G, st));
-  double2* F = d3 ? pen->G2 : pen->Gb;
   XformArgs az = xa;
   az.ne = fl.nf;
   RhsArgs r{};
   r.mode = 0;
-  HIP_TRY(launch_zf(az, pen->G, F, r, st));
-  HIP_TRY(launch_put_vars(xa.P, xa.S, xa.N, fl, F, X, st));
+  r.S = xa.S;
+  for (int f = 0; f < fl.nf; ++f) r.var[f] = fl.var[f];
+  HIP_TRY(launch_zf(az, pen->G, X, r, st));
   return STAU_OK;
 }
 

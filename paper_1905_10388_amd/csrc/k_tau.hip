@@ -72,155 +72,201 @@ __device__ __forceinline__ double first_flux(int c, double G, double sig, double
 }  // namespace
 
 // ---------------------------------------------------------------------------
-// Tables of one operator a0 M~ + L~.  One wavefront per block of KB
-// wavenumbers: six lanes per wavenumber eliminate (system, parity), then two
-// lanes form the unit-wall responses of the two parities, all in LDS; the
-// tables leave as one contiguous copy.  A serial chain of N / 2 pairs of
-// divisions bounds it.
+// Tables of one operator a0 M~ + L~, KB wavenumbers per block, all in LDS; the
+// tables leave as one contiguous copy.  Bound by the elimination's chain of N / 2
+// dependent divisions (six lanes per wavenumber: system, parity).  What is not a
+// recurrence runs over all threads by (wavenumber, degree), and the two
+// recurrences of the unit-wall response of psi have products and sums only
+// (64x64x64: 46 -> 23 us against six lanes doing everything; the banded LU
+// factors of the same operator 1520 us).
 // ---------------------------------------------------------------------------
-constexpr int kTauWork = 4;  // working arrays beside the tables: homogeneous fluxes, nu zeta
-__global__ void __launch_bounds__(kWave) tau_factor_kernel(int N, int nk, int KB, double a0, double kappa, double nu,
-                                                           const double* __restrict__ kmod, double* __restrict__ tab,
-                                                           double* __restrict__ scal) {
+constexpr int kTauWork = 4;  // working arrays beside the tables: b and homogeneous fluxes per system, nu zeta
+constexpr int kTauThreads = 256;
+__global__ void __launch_bounds__(kTauThreads) tau_factor_kernel(int N, int lgN, int nk, int KB, double a0,
+                                                                 double kappa, double nu,
+                                                                 const double* __restrict__ kmod,
+                                                                 double* __restrict__ tab, double* __restrict__ scal) {
   extern __shared__ double lds[];
-  const int lane = threadIdx.x;
+  const int tid = threadIdx.x;
   const int k0 = blockIdx.x * KB, nkb = min(KB, nk - k0);
   const int KS = (kTauArrays + kTauWork) * N + kTauScal + 1;  // stride per wavenumber
   const int n = N / 2;
-  {
-    const int kb = lane / 6, sys = (lane % 6) >> 1, par = lane & 1;
-    if (kb < nkb) {
-      double* T = lds + (size_t)kb * KS;
-      double* sc = T + (kTauArrays + kTauWork) * N;
-      const double k = kmod[k0 + kb], k2 = k * k;
-      const double x = sys == 0 ? (a0 + kappa * k2) / kappa : (sys == 1 ? (a0 + nu * k2) / nu : k2);
-      const double x8 = 0.125 * x;
-      double *rat = T + (2 * sys + kRatio) * N, *ui = T + (2 * sys + kUi) * N, *ph = T + (kTauArrays + sys) * N;
-      double r2 = 1.0;  // ratio_{m+2}
-      for (int j = n - 1; j >= 0; --j) {
-        const int m = 2 * j + par;
-        const double b = m + 1 <= N - 1 ? x8 / (double)(m + 1) * r2 : 0.0;
-        if (m == 0) {
-          rat[0] = ui[0] = 0.0;
-          ph[0] = 1.0;
-          sc[kScSys + 3 * sys + 2] = b;
-          break;
-        }
-        const double u = 2.0 * m + b;
-        const double A = m >= 2 ? x8 / (double)(m - 1) : 0.0;
-        ui[m] = 1.0 / u;
-        ph[m] = b;
-        r2 = u / (A + u);
-        rat[m] = r2;
+  double* inv = lds + (size_t)KB * KS;                        // 1 / m
+  auto T_of = [&](int kb) { return lds + (size_t)kb * KS; };
+  auto sc_of = [&](int kb) { return lds + (size_t)kb * KS + (kTauArrays + kTauWork) * N; };
+  // f(kb, m) for every wavenumber and degree
+  auto each = [&](auto&& f) {
+    for (int idx = tid; idx < nkb << lgN; idx += kTauThreads) f(idx >> lgN, idx & (N - 1));
+  };
+  for (int m = tid + 1; m <= N; m += kTauThreads) inv[m] = 1.0 / (double)m;
+  if (tid < nkb) sc_of(tid)[kScK] = kmod[k0 + tid];
+  __syncthreads();
+  const int kb6 = tid / 6, sys6 = (tid % 6) >> 1, par6 = tid & 1;
+  if (kb6 < nkb) {
+    double* T = T_of(kb6);
+    const double k = sc_of(kb6)[kScK], k2 = k * k;
+    const double x = sys6 == 0 ? (a0 + kappa * k2) / kappa : (sys6 == 1 ? (a0 + nu * k2) / nu : k2);
+    const double x8 = 0.125 * x;
+    double *rat = T + (2 * sys6 + kRatio) * N, *u_ = T + (2 * sys6 + kUi) * N, *ph = T + (kTauArrays + sys6) * N;
+    double r2 = 1.0;  // ratio_{m+2}
+    for (int j = n - 1; j >= 0; --j) {
+      const int m = 2 * j + par6;
+      const double b = m + 1 <= N - 1 ? x8 * inv[m + 1] * r2 : 0.0;
+      if (m == 0) {
+        rat[0] = 0.0;
+        ph[0] = b;
+        break;
       }
-      double v = 1.0, H = 0.0;
-      for (int j = par == 0 ? 1 : 0; j < n; ++j) {
-        const int m = 2 * j + par;
-        H = fma(v, ui[m], H);
-        v *= ph[m] * ui[m];
-        ph[m] = v;
-      }
-      sc[kScSys + 3 * sys + par] = H;
-      if (sys == 0 && par == 0) sc[kScK] = k;
+      const double u = 2.0 * m + b;
+      const double A = m >= 2 ? x8 * inv[m - 1] : 0.0;
+      u_[m] = u;
+      ph[m] = b;
+      r2 = u / (A + u);
+      rat[m] = r2;
     }
   }
   __syncthreads();
-  {
-    const int kb = lane >> 1, e = lane & 1;  // e: parity of eta, psi
-    if (kb < nkb) {
-      double* T = lds + (size_t)kb * KS;
-      double* sc = T + (kTauArrays + kTauWork) * N;
-      const double k = sc[kScK], k2 = k * k, al = a0 + nu * k2;
-      const double *uin = T + (2 + kUi) * N, *phn = T + (kTauArrays + 1) * N;
-      const double *rp = T + (4 + kRatio) * N, *uip = T + (4 + kUi) * N, *php = T + (kTauArrays + 2) * N;
-      double *he = T + kHe * N, *hp = T + kHp * N, *hu = T + kHu * N, *hs = T + (kTauArrays + 3) * N;
-      double* hpr = T + kHpr * N;
-      // eta with boundary sum 1, and nu zeta
-      const double* hn = sc + kScSys + 3;
-      const double st = first_flux(e, 1.0, 0.0, 0.0, hn);
-      if (e == 0)
-        he[0] = 1.0 - hn[0] * st;
-      else
-        hs[0] = nu * st;
-      double below = st;
-      for (int j = 0; j < n; ++j) {
-        const int m = 2 * j + e;
-        if (m >= 1) he[m] = below * uin[m];
-        below = st * phn[m];
-        if (m + 1 < N) hs[m + 1] = 2.0 * nu * below;
-      }
-      // C eta: the differences of eta cancel where al dominates; there al C eta =
-      // nu D zeta
-      auto ceta = [&](int m) -> double {
-        if (m > N - 2) return 0.0;
-        const double d = (double)(m + 1);
-        if (al > 4.0 * nu * d * d) return 2.0 * d * hs[m + 1] / al;
-        return cfac(m) * he[m] - (m + 2 < N ? 0.5 * he[m + 2] : 0.0);
-      };
-      // psi with boundary sum 0: S in hp, the particular fluxes in hu
-      const double x8 = 0.125 * k2;
-      double v = 0.0;
-      for (int j = n - 1; j >= 0; --j) {
-        const int m = 2 * j + e;
-        const double r2 = m + 2 < N ? rp[m + 2] : 1.0;
-        const double b = m + 1 <= N - 1 ? x8 / (double)(m + 1) * r2 : 0.0;
-        v = b * (m + 2 < N ? uip[m + 2] : 0.0) * v + r2 * (ceta(m) / (4.0 * (m + 1)));
-        hp[m] = v;
-      }
-      double sig = 0.0;
-      v = 0.0;
-      for (int j = 0; j < n; ++j) {
-        const int m = 2 * j + e;
-        const double r2 = m + 2 < N ? rp[m + 2] : 1.0;
-        const double b = m + 1 <= N - 1 ? x8 / (double)(m + 1) * r2 : 0.0;
-        sig += (v + hp[m]) * uip[m];
-        v = (b * v - 2.0 * m * hp[m]) * uip[m];
-        if (m + 1 < N) hu[m + 1] = v;
-      }
-      const double* hps = sc + kScSys + 6;
-      const double sp = first_flux(e, 0.0, sig, hp[0], hps);
-      double fl = sp, sum = 0.0;
-      for (int j = 0; j < n; ++j) {
-        const int m = 2 * j + e;
-        hp[m] = m == 0 ? -sig - hps[0] * sp : (fl + hp[m]) * uip[m];
-        if (m + 1 < N) {
-          fl = hu[m + 1] + sp * php[m];
-          hu[m + 1] = -2.0 * fl;
-          sum -= 2.0 * fl;
-        }
-      }
-      if (e == 1) {
-        hu[0] = -sp;
-        sum -= sp;
-        // t of the mean pencil: s_0 = a0 U_0 once sum U = 0
-        sc[kScMean] = hs[0] - a0 * (hu[0] - sum);
-      }
-      sc[kScU + e] = sum;
-      // p: D p = -a0 C w - nu k C eta where the degree exceeds k / 2, else k p = a0 U - s
-      for (int j = 0; j < n; ++j) {
-        const int m = 2 * j + 1 - e;
-        double p = 0.0;
-        if (m >= 1 && k < 2.0 * m) {
-          const int l = m - 1;
-          double ce = cfac(l) * he[l], cp = cfac(l) * hp[l];
-          if (l + 2 < N) {
-            ce -= 0.5 * he[l + 2];
-            cp -= 0.5 * hp[l + 2];
-          }
-          p = -k * (a0 * cp + nu * ce) / (2.0 * m);
-        } else if (k > 0.0) {
-          p = (a0 * hu[m] - hs[m]) / k;
-        }
-        hpr[m] = p;
+  each([&](int kb, int m) {
+    double* T = T_of(kb);
+#pragma unroll
+    for (int sys = 0; sys < 3; ++sys) {
+      double *ui = T + (2 * sys + kUi) * N, *ph = T + (kTauArrays + sys) * N;
+      if (m == 0) {
+        sc_of(kb)[kScSys + 3 * sys + 2] = ph[0];
+        ui[0] = 0.0;
+        ph[0] = 1.0;
+      } else {
+        const double v = 1.0 / ui[m];
+        ui[m] = v;
+        ph[m] *= v;
       }
     }
+  });
+  __syncthreads();
+  // homogeneous solutions with first flux 1
+  if (kb6 < nkb) {
+    double* T = T_of(kb6);
+    double *ui = T + (2 * sys6 + kUi) * N, *ph = T + (kTauArrays + sys6) * N;
+    double v = 1.0, H = 0.0;
+    for (int j = par6 == 0 ? 1 : 0; j < n; ++j) {
+      const int m = 2 * j + par6;
+      H = fma(v, ui[m], H);
+      v *= ph[m];
+      ph[m] = v;
+    }
+    sc_of(kb6)[kScSys + 3 * sys6 + par6] = H;
   }
+  __syncthreads();
+  // eta with boundary sum 1, and nu zeta
+  each([&](int kb, int m) {
+    double* T = T_of(kb);
+    const double* hn = sc_of(kb) + kScSys + 3;
+    const double *uin = T + (2 + kUi) * N, *phn = T + (kTauArrays + 1) * N;
+    double *he = T + kHe * N, *hs = T + (kTauArrays + 3) * N;
+    const double st = first_flux(m & 1, 1.0, 0.0, 0.0, hn);
+    he[m] = m == 0 ? 1.0 - hn[0] * st : (m >= 2 ? st * phn[m - 2] : st) * uin[m];
+    if (m + 1 < N) hs[m + 1] = 2.0 * nu * (st * phn[m]);
+    if (m == 1) hs[0] = nu * st;
+  });
+  __syncthreads();
+  // psi with boundary sum 0: the sources of S in hp, b and the factors of S in the
+  // working arrays of b and eta
+  each([&](int kb, int m) {
+    double* T = T_of(kb);
+    const double k = sc_of(kb)[kScK], k2 = k * k, al = a0 + nu * k2;
+    const double *he = T + kHe * N, *hs = T + (kTauArrays + 3) * N;
+    const double *rp = T + (4 + kRatio) * N, *uip = T + (4 + kUi) * N;
+    const double r2 = m + 2 < N ? rp[m + 2] : 1.0;
+    const double b = m + 1 <= N - 1 ? 0.125 * k2 * inv[m + 1] * r2 : 0.0;
+    // C eta: the differences of eta cancel where al dominates; there al C eta =
+    // nu D zeta
+    double ce = 0.0;
+    if (m <= N - 2) {
+      const double d = (double)(m + 1);
+      ce = al > 4.0 * nu * d * d ? 2.0 * d * hs[m + 1] / al : cfac(m) * he[m] - (m + 2 < N ? 0.5 * he[m + 2] : 0.0);
+    }
+    T[kHp * N + m] = r2 * (0.25 * ce * inv[m + 1]);
+    T[kTauArrays * N + m] = b;
+    T[(kTauArrays + 1) * N + m] = b * (m + 2 < N ? uip[m + 2] : 0.0);
+  });
+  __syncthreads();
+  const int kb2 = tid >> 1, e2 = tid & 1;  // e: parity of eta, psi
+  if (kb2 < nkb) {
+    double *T = T_of(kb2), *sc = sc_of(kb2);
+    const double *uip = T + (4 + kUi) * N, *bp = T + kTauArrays * N, *alp = T + (kTauArrays + 1) * N;
+    double *hp = T + kHp * N, *hu = T + kHu * N;
+    double v = 0.0;
+    for (int j = n - 1; j >= 0; --j) {
+      const int m = 2 * j + e2;
+      v = fma(alp[m], v, hp[m]);
+      hp[m] = v;
+    }
+    double sig = 0.0;
+    v = 0.0;
+    for (int j = 0; j < n; ++j) {
+      const int m = 2 * j + e2;
+      const double ui = uip[m], S = hp[m];
+      sig = fma(v + S, ui, sig);
+      v = fma(bp[m], v, -2.0 * m * S) * ui;
+      if (m + 1 < N) hu[m + 1] = v;
+    }
+    // (the sums of U's place holds the first fluxes, kScMean's and the unused slot
+    // behind the scalars the sums of the particular psi until they are used)
+    sc[kScU + e2] = first_flux(e2, 0.0, sig, hp[e2 ? 1 : 0], sc + kScSys + 6);
+    sc[kScMean + e2] = sig;
+  }
+  __syncthreads();
+  // psi, then U = -psi_z, each in place
+  each([&](int kb, int m) {
+    double* T = T_of(kb);
+    const double* sc = sc_of(kb);
+    const double sp = sc[kScU + (m & 1)];
+    const double fl = m >= 2 ? T[kHu * N + m - 1] + sp * T[(kTauArrays + 2) * N + m - 2] : sp;
+    T[kHp * N + m] = m == 0 ? -sc[kScMean] - sc[kScSys + 6] * sp : (fl + T[kHp * N + m]) * T[(4 + kUi) * N + m];
+  });
+  __syncthreads();
+  each([&](int kb, int m) {
+    double* T = T_of(kb);
+    const double* sc = sc_of(kb);
+    double* hu = T + kHu * N;
+    if (m + 1 < N) hu[m + 1] = -2.0 * (hu[m + 1] + sc[kScU + (m & 1)] * T[(kTauArrays + 2) * N + m]);
+    if (m == 1) hu[0] = -sc[kScU + 1];
+  });
+  __syncthreads();
+  if (kb2 < nkb) {
+    double *T = T_of(kb2), *sc = sc_of(kb2);
+    const double *hu = T + kHu * N, *hs = T + (kTauArrays + 3) * N;
+    double sum = 0.0;
+    for (int m = 1 - e2; m < N; m += 2) sum += hu[m];
+    // t of the mean pencil: s_0 = a0 U_0 once sum U = 0
+    if (e2 == 1) sc[kScMean] = hs[0] - a0 * (hu[0] - sum);
+    sc[kScU + e2] = sum;
+  }
+  // p: D p = -a0 C w - nu k C eta where the degree exceeds k / 2, else k p = a0 U - s
+  each([&](int kb, int m) {
+    double* T = T_of(kb);
+    const double k = sc_of(kb)[kScK];
+    const double *he = T + kHe * N, *hp = T + kHp * N;
+    double p = 0.0;
+    if (m >= 1 && k < 2.0 * m) {
+      const int l = m - 1;
+      double ce = cfac(l) * he[l], cp = cfac(l) * hp[l];
+      if (l + 2 < N) {
+        ce -= 0.5 * he[l + 2];
+        cp -= 0.5 * hp[l + 2];
+      }
+      p = -0.5 * k * (a0 * cp + nu * ce) * inv[m];
+    } else if (k > 0.0) {
+      p = (a0 * T[kHu * N + m] - T[(kTauArrays + 3) * N + m]) / k;
+    }
+    T[kHpr * N + m] = p;
+  });
   __syncthreads();
   const int per = kTauArrays * N;
   for (int kb = 0; kb < nkb; ++kb) {
-    const double* T = lds + (size_t)kb * KS;
-    for (int i = lane; i < per; i += kWave) tab[(size_t)(k0 + kb) * per + i] = T[i];
-    if (lane < kTauScal) scal[(size_t)(k0 + kb) * kTauScal + lane] = T[(kTauArrays + kTauWork) * N + lane];
+    const double* T = T_of(kb);
+    for (int i = tid; i < per; i += kTauThreads) tab[(size_t)(k0 + kb) * per + i] = T[i];
+    if (tid < kTauScal) scal[(size_t)(k0 + kb) * kTauScal + tid] = sc_of(kb)[tid];
   }
 }
 
@@ -366,6 +412,9 @@ __device__ __forceinline__ double2 operator-(double2 a, double2 b) { return make
 // independent systems run on different wavefronts.  LDS per pencil: NA arrays
 // (b and its fluxes, then psi's; eta's; phi; g; 3-D: the normal velocity's)
 // and four coefficient arrays (b, 1 / u of b, then of psi; of eta).
+// Bound by the memory at the large sizes (256x256x128: 297 us, 0.95 GB; one lane
+// per chain 766, the banded sweeps 3195), by the three chains' latency at the
+// small ones (1024x256: 16 us, 47, 124; 4096x64: 16, 26, 95; 64x32: 9.5, -, 20).
 // ---------------------------------------------------------------------------
 template <int DIM, int E>
 __global__ void __launch_bounds__(E > 8 ? 512 : 256) tau_solve_kernel(PencilArgs a, TauFactors tf, double a0, int NP,
@@ -611,13 +660,17 @@ static void allow_lds(const void* fn, size_t bytes) {
 
 hipError_t launch_tau_factor(const PencilArgs& a, double a0, const TauFactors& tf, hipStream_t st) {
   const int N = a.desc.N;
-  // six lanes per wavenumber, at most half a compute unit's LDS per block
+  // up to eight wavenumbers per block in half a compute unit's LDS, fewer while
+  // that leaves units without a block
   const size_t per = (size_t)((kTauArrays + kTauWork) * N + kTauScal + 1) * sizeof(double);
-  const int KB = (int)std::max<size_t>(1, std::min<size_t>(8, (size_t)(80 * 1024) / per));
-  const size_t lds = KB * per;
+  int KB = (int)std::max<size_t>(1, std::min<size_t>(8, (size_t)(72 * 1024) / per));
+  while (KB > 1 && (tf.nk + KB - 1) / KB < tf.cus) --KB;
+  const size_t lds = KB * per + (size_t)(N + 1) * sizeof(double);
+  int lgN = 0;
+  while ((1 << lgN) < N) ++lgN;
   allow_lds((const void*)tau_factor_kernel, lds);
-  hipLaunchKernelGGL(tau_factor_kernel, dim3((tf.nk + KB - 1) / KB), dim3(kWave), lds, st, N, tf.nk, KB, a0, a.kappa,
-                     a.nu, tf.k, tf.tab, tf.scal);
+  hipLaunchKernelGGL(tau_factor_kernel, dim3((tf.nk + KB - 1) / KB), dim3(kTauThreads), lds, st, N, lgN, tf.nk, KB, a0,
+                     a.kappa, a.nu, tf.k, tf.tab, tf.scal);
   return hipGetLastError();
 }
 

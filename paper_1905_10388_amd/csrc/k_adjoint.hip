@@ -1,7 +1,7 @@
 // Adjoint transform kernels of the discrete adjoint step: the transposes of
 // the z transforms, of the fused x pass and of the kinetic-energy and
 // initial-state maps.
-#include "xform.h"
+#include "xrow.h"
 
 namespace stau {
 
@@ -258,6 +258,184 @@ __global__ void __launch_bounds__(NT) xpass_adj_kernel(XformArgs a,
   }
 }
 
+// The same in FP64 at the compile-time row lengths (XRow), always two blocks per
+// row: blockIdx.y 0 synthesises H_bar and the derivative pairs for the (u, w)
+// outputs, 1 synthesises H_bar and (u, w) for the derivative outputs.  Bound by
+// its chain of transforms (adjoint step with this and zadj_fft_kernel against
+// the in-place kernels: 512x128 120 -> 97 us, 4096x32 192 -> 144, 256x64 90 -> 65;
+// the transposed solve has 56 of the 97).
+template <typename PL, int NB2, int WPE>
+__global__ void __launch_bounds__((XRow<PL, 1, NB2>::NT)) __attribute__((amdgpu_waves_per_eu(WPE)))
+    xadj_fft_kernel(XformArgs a, const double2* __restrict__ G, const double2* __restrict__ Hb,
+                    double2* __restrict__ Gb) {
+  extern __shared__ double2 smem[];
+  using X = XRow<PL, 1, NB2>;
+  using T = double;
+  using cT = cpx<T>;
+  constexpr int PT = X::PT, P = X::Pa + 1;
+  X x(smem, a, 1);
+  const size_t row = (size_t)blockIdx.x * P, R = (size_t)a.M * P;
+  // pairs 0..3 the forward fields (G 0..7), 4 (Hb 0, Hb 1) and 5 (Hb 2, -): these
+  // with weight 1/2 for k >= 1, here 2 for k = 0 and 1/2 in hf
+  auto pair = [&](int k) {
+    if (k < 4) return XSrc{G + row + 2 * k * R, G + row + (2 * k + 1) * R, false, false, 1.0};
+    return XSrc{Hb + row + 2 * (k - 4) * R, k == 4 ? Hb + row + R : nullptr, false, false, 2.0};
+  };
+  const T hf = (T)0.5 / (T)X::L;
+  T nb[PT], nu[PT], nw[PT], s[PT], t[PT];  // s, t: the (u, w) adjoints, or u and w
+  // pair K of one or two transformed together
+  auto take = [&](auto kc, const cT* v) __attribute__((always_inline)) {
+    constexpr int K = decltype(kc)::value;
+#pragma unroll
+    for (int q = 0; q < PT; ++q) {
+      const T f = v[q].x, g = v[q].y;
+      if (K == 0) { s[q] = f; t[q] = g; }
+      if (K == 1) { s[q] = -(nb[q] * f); t[q] = -(nb[q] * g); }
+      if (K == 2) { s[q] -= nu[q] * f; t[q] -= nu[q] * g; }
+      if (K == 3) { s[q] -= nw[q] * f; t[q] -= nw[q] * g; }
+      if (K == 4) { nb[q] = hf * f; nu[q] = hf * g; }
+      if (K == 5) nw[q] = hf * f;
+    }
+  };
+  auto run1 = [&](auto kc) __attribute__((always_inline)) {
+    constexpr int K = decltype(kc)::value;
+    x.template backward<1>([&](int, int) { return pair(K); },
+                           [&](auto, const cT* v) __attribute__((always_inline)) { take(kc, v); });
+  };
+  auto run2 = [&](auto k0, auto k1) __attribute__((always_inline)) {
+    constexpr int K0 = decltype(k0)::value, K1 = decltype(k1)::value;
+    if constexpr (NB2 >= 2) {
+      x.template backward<2>([&](int, int p) { return pair(p ? K1 : K0); },
+                             [&](auto pc, const cT* v) __attribute__((always_inline)) {
+                               take(std::integral_constant<int, decltype(pc)::value ? K1 : K0>{}, v);
+                             });
+    } else {
+      run1(k0);
+      run1(k1);
+    }
+  };
+  // adjoint of a synthesis: weights 1 (k = 0) and 2
+  auto out = [&](int f) { return XDst{Gb + row + f * R, Gb + row + (f + 1) * R, 0.5, 1.0}; };
+  auto deriv = [&](auto fc, cT* v) __attribute__((always_inline)) {  // outputs -n_f (u, w)
+    constexpr int F = decltype(fc)::value;
+#pragma unroll
+    for (int q = 0; q < PT; ++q) {
+      const T n = F == 0 ? nb[q] : F == 1 ? nu[q] : nw[q];
+      v[q] = mk<T>(-n * s[q], -n * t[q]);
+    }
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
+  using I4 = std::integral_constant<int, 4>;
+  using I5 = std::integral_constant<int, 5>;
+  run2(I4{}, I5{});
+  if (blockIdx.y == 0) {
+    run2(I1{}, I2{});
+    run1(I3{});
+    x.template forward<1>(
+        [&](auto, cT* v) __attribute__((always_inline)) {
+#pragma unroll
+          for (int q = 0; q < PT; ++q) v[q] = mk<T>(s[q], t[q]);
+        },
+        [&](int, int) { return out(0); });
+  } else {
+    run1(I0{});
+    if constexpr (NB2 >= 2) {
+      x.template forward<2>([&](auto pc, cT* v) __attribute__((always_inline)) { deriv(pc, v); },
+                            [&](int, int p) { return out(2 + 2 * p); });
+    } else {
+      x.template forward<1>([&](auto, cT* v) __attribute__((always_inline)) { deriv(I0{}, v); },
+                            [&](int, int) { return out(2); });
+      x.template forward<1>([&](auto, cT* v) __attribute__((always_inline)) { deriv(I1{}, v); },
+                            [&](int, int) { return out(4); });
+    }
+    x.template forward<1>([&](auto, cT* v) __attribute__((always_inline)) { deriv(I2{}, v); },
+                          [&](int, int) { return out(6); });
+  }
+}
+
+// The z adjoint in FP64 at the dealiased lengths (as zf_fft_kernel): a thread's two
+// last-stage butterflies hold V_n and V_{M-n}, their sum over the sources stays in
+// registers.
+template <typename PL, int TP, int NT>
+__global__ void __launch_bounds__(NT) zadj_fft_kernel(XformArgs a, AccList al, const double2* __restrict__ Gb,
+                                                      double2* __restrict__ Xb) {
+  extern __shared__ double2 smem[];
+  constexpr int M = PL::L, N = M / 3 * 2, R0 = PL::r[0], W0 = M / R0, RL = PL::PT, W = M / RL, U = W / 2,
+                QN = RL / 3 * 2;
+  static_assert(RL % 3 == 0 && TP * U <= NT, "thirds of the last stage, one pair of butterflies per thread");
+  cd* buf = (cd*)smem;
+  const int ti = blockIdx.y, p0 = blockIdx.x * TP, tid = threadIdx.x;
+  const PencilBase pb = pencil_base(a, p0);
+  auto at = [](int s, int i) { return s * (M + 1) + i; };
+  auto sel = [](bool c, cd x, cd y) { return mk(c ? x.x : y.x, c ? x.y : y.y); };
+  const int s0 = tid % TP, t = tid / TP;
+  const bool own = t < U;
+  const int j1 = t, j2 = t ? W - t : U;
+  cd acc1[QN], acc2[QN];
+#pragma unroll
+  for (int q = 0; q < QN; ++q) acc1[q] = acc2[q] = mk(0.0, 0.0);
+  for (int src = 0; src < al.nsrc[ti]; ++src) {
+    const int f = al.src[ti][src], der = al.deriv[ti][src];
+    auto load = [&](int, int s, int j, cd* v) {
+      const double2* h = Gb + (size_t)f * M * a.P + p0 + s;
+      const bool in = p0 + s < a.P;
+#pragma unroll
+      for (int q = 0; q < R0; ++q) {
+        const int i = j + q * W0, jz = 2 * i < M ? 2 * i : 2 * (M - 1 - i) + 1;
+        v[q] = in ? ld2(h + (size_t)jz * a.P) : mk(0.0, 0.0);
+      }
+    };
+    fft_block<PL, -1, TP, NT, true, true, false, double>(buf, (const cd*)a.twz, tid, load, [](int, int, cd*) {}, at);
+    if (own) {
+      cd v1[RL], v2[RL];
+#pragma unroll
+      for (int q = 0; q < RL; ++q) {
+        v1[q] = buf[at(s0, j1 + q * W)];
+        v2[q] = buf[at(s0, j2 + q * W)];
+      }
+      fft_butterfly<M, RL, W, -1, double>(v1, j1, (const cd*)a.twz);
+      fft_butterfly<M, RL, W, -1, double>(v2, j2, (const cd*)a.twz);
+      const double kk = der == 0 ? 0.0 : der == 1 ? kx_at(a, pb, s0) : ky_at(a, pb, s0);
+      auto add = [&](cd& acc, int n, cd V, cd Vm) {
+        const cd w = conj(ld2(a.dctz + n));
+        const cd P = cmul(w, V), Q = cmul(w, conj(Vm));
+        const double sc = n & 1 ? -0.5 : 0.5;
+        cd Y = mk(sc * (P.x + Q.x), sc * (P.y - Q.y));
+        if (der) Y = mk(kk * Y.y, -kk * Y.x);  // conj(i k) Y = -i k Y
+        acc = acc + Y;
+      };
+#pragma unroll
+      for (int q = 0; q < QN; ++q) {
+        add(acc1[q], j1 + q * W, v1[q], sel(t, v2[RL - 1 - q], v1[q ? RL - q : 0]));
+        add(acc2[q], j2 + q * W, v2[q], sel(t, v1[RL - 1 - q], v2[RL - 1 - q]));
+      }
+    }
+    __syncthreads();
+  }
+  if (own) {
+#pragma unroll
+    for (int q = 0; q < QN; ++q) {
+      buf[at(s0, j1 + q * W)] = acc1[q];
+      buf[at(s0, j2 + q * W)] = acc2[q];
+    }
+  }
+  __syncthreads();
+  const int var = al.target[ti];
+#pragma unroll 4
+  for (int idx = tid; idx < TP * N; idx += NT) {
+    const int s = idx / N, nn = idx - s * N;
+    if (active_at(a, pb, s)) {
+      double2* o = Xb + ((size_t)(p0 + s) * a.S + var) * N + nn;
+      const cd v = buf[at(s, nn)];
+      const double2 old = *o;
+      *o = make_double2(old.x + v.x, old.y + v.y);
+    }
+  }
+}
+
 // Kinetic-energy adjoint for one row: u_bar = e_bar_j u, w_bar = e_bar_j w with
 // e_bar_j = (1/L) sum_m w_m (2 - delta)/M T_m(z_j) (precomputed in ebar).
 template <int MAXBF, int PTS, int NT>
@@ -384,8 +562,38 @@ __global__ void __launch_bounds__(256) ic_adj_x_kernel(XformArgs a, const double
   for (int i = tid; i < Nx; i += nt) gbar[(size_t)i * N + jz] = buf[i].x * inv;
 }
 
+template <typename PL, int TP, int NT>
+static hipError_t launch_zadj_fft(const XformArgs& a, const AccList& al, const void* Gbar, void* Xbar,
+                                  hipStream_t st) {
+  constexpr size_t lds = (size_t)TP * (PL::L + 1) * sizeof(double2);
+  auto fn = zadj_fft_kernel<PL, TP, NT>;
+  allow_lds((const void*)fn, lds);
+  hipLaunchKernelGGL(fn, dim3((a.P + TP - 1) / TP, al.nt), dim3(NT), lds, st, a, al, (const double2*)Gbar,
+                     (double2*)Xbar);
+  return hipGetLastError();
+}
+
 hipError_t launch_zadj(const XformArgs& a, const AccList& al, const void* Gbar, void* Xbar,
                        hipStream_t st, bool fp32) {
+  if (!fp32 && 2 * a.M == 3 * a.N) {
+    const bool few = (a.P + 7) / 8 * al.nt < 2 * unit_count();  // (as in launch_zb)
+    switch (a.M) {
+      case 24: return launch_zadj_fft<FftPlan<4, 6>, 8, 64>(a, al, Gbar, Xbar, st);
+      case 48:
+        return few ? launch_zadj_fft<FftPlan<8, 6>, 4, 64>(a, al, Gbar, Xbar, st)
+                   : launch_zadj_fft<FftPlan<8, 6>, 8, 64>(a, al, Gbar, Xbar, st);
+      case 96:
+        return few ? launch_zadj_fft<FftPlan<4, 4, 6>, 4, 64>(a, al, Gbar, Xbar, st)
+                   : launch_zadj_fft<FftPlan<4, 4, 6>, 8, 128>(a, al, Gbar, Xbar, st);
+      case 192:
+        return few ? launch_zadj_fft<FftPlan<4, 8, 6>, 4, 128>(a, al, Gbar, Xbar, st)
+                   : launch_zadj_fft<FftPlan<4, 8, 6>, 8, 128>(a, al, Gbar, Xbar, st);
+      case 384:
+        return few ? launch_zadj_fft<FftPlan<8, 8, 6>, 4, 256>(a, al, Gbar, Xbar, st)
+                   : launch_zadj_fft<FftPlan<8, 8, 6>, 8, 256>(a, al, Gbar, Xbar, st);
+      case 768: return launch_zadj_fft<FftPlan<8, 4, 4, 6>, 4, 256>(a, al, Gbar, Xbar, st);
+    }
+  }
   int TP = z_tile(a.M);
   if (TP * a.M != kZPts || TP * a.N > 12 * kZThreads) return hipErrorInvalidValue;
   // half-size tiles when the full-size grid has fewer blocks than compute
@@ -439,18 +647,42 @@ static hipError_t launch_xpass_adj_t(const XformArgs& a, const void* G, const vo
   return hipGetLastError();
 }
 
+template <int NB2, int WPE, int... R>
+static hipError_t launch_xadj_fft(const XformArgs& a, const void* G, const void* Hb, void* Gb, hipStream_t st) {
+  using X = XRow<FftPlan<R...>, 1, NB2>;
+  auto fn = xadj_fft_kernel<FftPlan<R...>, NB2, WPE>;
+  allow_lds((const void*)fn, X::lds);
+  hipLaunchKernelGGL(fn, dim3(a.M, 2), dim3(X::NT), X::lds, st, a, (const double2*)G, (const double2*)Hb,
+                     (double2*)Gb);
+  return hipGetLastError();
+}
+
 template <typename T>
 static hipError_t launch_xpass_adj_T(const XformArgs& a, const void* G, const void* Hb, void* Gb,
                                      hipStream_t st) {
   const int L = a.L;
+  // (the radices of the x pass)
+  if (sizeof(T) == 8) switch (L) {
+    case 24: return launch_xadj_fft<2, 2, 6, 4>(a, G, Hb, Gb, st);
+    case 48: return launch_xadj_fft<2, 2, 3, 4, 4>(a, G, Hb, Gb, st);
+    case 96: return launch_xadj_fft<2, 2, 3, 8, 4>(a, G, Hb, Gb, st);
+    case 192: return launch_xadj_fft<2, 2, 3, 8, 8>(a, G, Hb, Gb, st);
+    case 384: return launch_xadj_fft<2, 2, 6, 8, 8>(a, G, Hb, Gb, st);
+    case 768: return launch_xadj_fft<2, 2, 6, 16, 8>(a, G, Hb, Gb, st);
+    case 1536: return launch_xadj_fft<2, 2, 3, 8, 8, 8>(a, G, Hb, Gb, st);
+    case 3072: return launch_xadj_fft<2, 2, 6, 8, 8, 8>(a, G, Hb, Gb, st);
+    case 6144: return launch_xadj_fft<1, 3, 6, 16, 8, 8>(a, G, Hb, Gb, st);
+  }
   if (L <= 64) return launch_xpass_adj_t<64, 1, 1, T>(a, G, Hb, Gb, st);
-  if (L <= 128) return launch_xpass_adj_t<64, 2, 1, T>(a, G, Hb, Gb, st);
-  if (L <= 192) return launch_xpass_adj_t<64, 3, 1, T>(a, G, Hb, Gb, st);
-  if (L <= 384) return launch_xpass_adj_t<128, 3, 1, T>(a, G, Hb, Gb, st);
-  if (L <= 768) return launch_xpass_adj_t<256, 3, 1, T>(a, G, Hb, Gb, st);
-  if (L <= 1536) return launch_xpass_adj_t<512, 3, 1, T>(a, G, Hb, Gb, st);
-  if (L <= 3072) return launch_xpass_adj_t<1024, 3, 1, T>(a, G, Hb, Gb, st);
-  if (L <= 6144) return launch_xpass_adj_t<1024, 6, 2, T>(a, G, Hb, Gb, st);
+  if constexpr (sizeof(T) == 4) {
+    if (L <= 128) return launch_xpass_adj_t<64, 2, 1, T>(a, G, Hb, Gb, st);
+    if (L <= 192) return launch_xpass_adj_t<64, 3, 1, T>(a, G, Hb, Gb, st);
+    if (L <= 384) return launch_xpass_adj_t<128, 3, 1, T>(a, G, Hb, Gb, st);
+    if (L <= 768) return launch_xpass_adj_t<256, 3, 1, T>(a, G, Hb, Gb, st);
+    if (L <= 1536) return launch_xpass_adj_t<512, 3, 1, T>(a, G, Hb, Gb, st);
+    if (L <= 3072) return launch_xpass_adj_t<1024, 3, 1, T>(a, G, Hb, Gb, st);
+    if (L <= 6144) return launch_xpass_adj_t<1024, 6, 2, T>(a, G, Hb, Gb, st);
+  }
   return hipErrorInvalidValue;
 }
 

@@ -2,8 +2,7 @@
 // dealiasing", Sec. VII "Arithmetic operators"): per dealiased row, packed
 // complex-to-real transforms of the grid fields, the products, and packed
 // real-to-complex transforms truncated to the stored modes (2-D and 3-D).
-#include "fft.h"
-#include "xform.h"
+#include "xrow.h"
 
 namespace stau {
 
@@ -483,288 +482,78 @@ __global__ void __launch_bounds__(NT) xrow3_kernel(XformArgs a,
 }
 
 // ---------------------------------------------------------------------------
-// The FP64 x pass at compile-time row lengths L = 3 Nx / 2, from registers to
-// registers: NR rows per block, PT = the last radix, L / PT threads per row, NB2
-// pairs at a time.  The forward transforms run the backward stages in reverse:
-//   * first backward stage, radix R0 = 3 Q: butterfly j takes the entries
-//     j + r W (W = L / R0).  Those of the middle third are the padding, known to
-//     be zero; those of the upper third are the conjugate-symmetric partners of
-//     the lower third's entries of butterfly W - j, so a thread that does both
-//     butterflies reads every entry of the half spectra once;
-//   * last backward stage: a thread owns the grid points j + r L / PT, r < PT, of its
-//     row for every pair, forms the products there and starts the forward
-//     transforms, whose first radix is PT too, from them;
-//   * last forward stage: butterflies j and W - j again hold each entry and its
-//     partner, so the two real fields of a sequence separate in registers; the
-//     dropped third is never formed.
-// Between two stages a sequence goes through LDS once (L = 384: 4 accesses per
-// element), where the in-place transforms of xrow2_kernel and xrow3_kernel have
-// two per pass and two at each end (8 to 10).  Those kernels were bound by LDS
-// and FP64 arithmetic about equally (L = 384: LDS busy for 57 % of the time,
-// arithmetic for 52 %; the memory's share 60 %); the small launches by their
-// chains of passes and, with lengths known at run time only, integer divisions.
-// The stages between the ends are spread over the block by (row, pair,
-// butterfly).  FP32 keeps the in-place kernels (see ypass_fft_kernel).
+// The FP64 x pass at compile-time row lengths (XRow).  The in-place transforms of
+// xrow2_kernel and xrow3_kernel have two LDS accesses per element and pass and
+// two at each end (L = 384: 8 to 10 against 4 here) and were bound by LDS and FP64
+// arithmetic about equally (L = 384: LDS busy for 57 % of the time, arithmetic
+// for 52 %; the memory's share 60 %), the small launches by their chains of
+// passes and, with lengths known at run time only, integer divisions.  FP32
+// keeps the in-place kernels (see ypass_fft_kernel).
 // 2-D: two blocks per row, blockIdx.y = 0 forms N_b and N_u, 1 forms N_w.
 // ---------------------------------------------------------------------------
-// sequence length in LDS: at radix 12 one entry of padding per 12 (the first
-// stage's writes are R0 entries apart)
-template <typename PL>
-constexpr int xseq() { return PL::r[0] == 12 ? PL::L / 12 * 13 : PL::L; }
-
 template <int DIM, typename PL, int NR, int NB2, int WPE>
-__global__ void __launch_bounds__((NR * (PL::L / PL::PT) + 63) / 64 * 64) __attribute__((amdgpu_waves_per_eu(WPE)))
+__global__ void __launch_bounds__((XRow<PL, NR, NB2>::NT)) __attribute__((amdgpu_waves_per_eu(WPE)))
     xrow_fft_kernel(XformArgs a, const double2* __restrict__ G, double2* __restrict__ H, int rows) {
   extern __shared__ double2 smem[];
+  using X = XRow<PL, NR, NB2>;
   using T = double;
   using cT = cpx<T>;
-  constexpr int L = PL::L, PT = PL::PT;
-  constexpr int TR = L / PT, R0 = PL::r[0], Q = R0 / 3, W = L / R0, U = W / 2, Pa = L / 3, Px = Pa + 1;
-  constexpr int LS = xseq<PL>(), NST = PL::n, NT = (NR * TR + 63) / 64 * 64;
-  const int tid = threadIdx.x, row = tid / TR, tj = tid - row * TR;
-  const int r0 = blockIdx.x * NR, nrow = rows - r0 < NR ? rows - r0 : NR;
-  const bool on = row < nrow;
+  constexpr int PT = X::PT, Px = X::Pa + 1;
+  const int r0 = blockIdx.x * NR;
+  X x(smem, a, rows - r0 < NR ? rows - r0 : NR);
   const size_t R = (size_t)a.M * (DIM == 3 ? a.Ngy : 1);
-  cT* buf = (cT*)smem;  // [row][sequence][LS]
-  const cT* tw = (const cT*)a.twx;
-  // LDS places: backward padded by R0 = 12; forward the low three bits of the
-  // index exchanged with the next three (the first stage writes PT apart)
-  auto atb = [](int i) { return R0 == 12 ? i + i / 12 : i; };
-  auto atf = [](int i) { return i ^ ((i >> 3) & 7); };
-  // (by value: a choice between two elements of register arrays by reference
-  // would put both arrays into scratch memory)
-  auto sel = [](bool c, cT x, cT y) { return mk<T>(c ? x.x : y.x, c ? x.y : y.y); };
-
-  // stages 1 .. NST - 2 of the backward (DIR +1) or forward transform of `count`
-  // (a constant) sequences per row: items (row, sequence, butterfly) over the block
-  auto middle = [&](auto dirc, auto cntc) __attribute__((always_inline)) {
-    constexpr int DIR = decltype(dirc)::value, NC = decltype(cntc)::value;
-    static_for_stage<1, NST - 1>([&](auto sc) {
-      constexpr int S = decltype(sc)::value;
-      constexpr int RS = DIR > 0 ? PL::r[S] : PL::r[NST - 1 - S], WS = L / RS;
-      constexpr int NS = [] {
-        int p = 1;
-        for (int q = 0; q < S; ++q) p *= DIR > 0 ? PL::r[q] : PL::r[NST - 1 - q];
-        return p;
-      }();
-      constexpr int IT = NR * NC * WS, NB = (IT + NT - 1) / NT;
-      cT v[NB][RS];
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const int it = tid + b * NT, sq = it / WS, j = it - sq * WS;
-        const cT* B = buf + ((sq / NC) * NB2 + sq % NC) * LS;
-        if (IT % NT == 0 || it < IT) {
-#pragma unroll
-          for (int q = 0; q < RS; ++q) v[b][q] = B[DIR > 0 ? atb(j + q * WS) : atf(j + q * WS)];
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const int it = tid + b * NT, sq = it / WS, j = it - sq * WS;
-        cT* B = buf + ((sq / NC) * NB2 + sq % NC) * LS;
-        if (IT % NT == 0 || it < IT) {
-          fft_butterfly<L, RS, NS, DIR, T>(v[b], j, tw);
-          const int o = (j / NS) * NS * RS + j % NS;
-#pragma unroll
-          for (int q = 0; q < RS; ++q) B[DIR > 0 ? atb(o + q * NS) : atf(o + q * NS)] = v[b][q];
-        }
-      }
-      __syncthreads();
-    });
+  auto pair = [&](int rw, int k) {
+    int fa, da, fb, db;
+    pair_src<DIM>(k, fa, da, fb, db);
+    const double2* g = G + (size_t)(r0 + rw) * Px;
+    return XSrc{g + (size_t)fa * R * Px, fb < 0 ? nullptr : g + (size_t)fb * R * Px, da != 0, db != 0, 1.0};
   };
-
-  // backward transforms of NC pairs, pair i being pk(i); take(i, v): the PT grid
-  // points of pair i, real and imaginary parts the pair's two fields
-  auto backward = [&](auto cntc, auto&& pk, auto&& take) __attribute__((always_inline)) {
-    constexpr int NC = decltype(cntc)::value;
-    constexpr int IT = NR * NC * U, NB = (IT + NT - 1) / NT;
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int it = tid + b * NT, sq = it / U, t = it - sq * U, rw = sq / NC, p = sq % NC;
-      if (rw >= nrow) continue;
-      const int j1 = t, j2 = t ? W - t : U, r = r0 + rw;
-      cT* B = buf + (rw * NB2 + p) * LS;
-      int fa, da, fb, db;
-      pair_src<DIM>(pk(p), fa, da, fb, db);
-      const double2* Ga = G + ((size_t)fa * R + r) * Px;
-      const double2* Gb = G + ((size_t)(fb < 0 ? fa : fb) * R + r) * Px;
-      cT a1[Q], a2[Q], b1[Q], b2[Q];
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        a1[q] = ldv<T>(Ga + j1 + q * W);
-        a2[q] = ldv<T>(Ga + j2 + q * W);
-        b1[q] = b2[q] = mk<T>(0, 0);
-        if (fb >= 0) {
-          b1[q] = ldv<T>(Gb + j1 + q * W);
-          b2[q] = ldv<T>(Gb + j2 + q * W);
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        if (da) {
-          a1[q] = ikx<T>(a, j1 + q * W, a1[q]);
-          a2[q] = ikx<T>(a, j2 + q * W, a2[q]);
-        }
-        if (db) {
-          b1[q] = ikx<T>(a, j1 + q * W, b1[q]);
-          b2[q] = ikx<T>(a, j2 + q * W, b2[q]);
-        }
-      }
-      if (t == 0) a1[0].y = b1[0].y = 0;  // k = 0: real
-      cT v[R0];
-      // entries of butterfly j1: the lower third from (a1, b1), the upper third
-      // the partners of the lower one's entries of j2 (j1 = 0: its own)
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        v[q] = mk<T>(a1[q].x - b1[q].y, a1[q].y + b1[q].x);
-        v[Q + q] = mk<T>(0, 0);
-        const cT c2 = mk<T>(a2[q].x + b2[q].y, -a2[q].y + b2[q].x);
-        cT n1 = mk<T>(0, 0);  // (j1 = 0: k = (q + 1) W, padding for q = Q - 1)
-        if constexpr (Q > 1) {
-          if (q + 1 < Q) n1 = mk<T>(a1[(q + 1) % Q].x + b1[(q + 1) % Q].y, -a1[(q + 1) % Q].y + b1[(q + 1) % Q].x);
-        }
-        v[R0 - 1 - q] = sel(t, c2, n1);
-      }
-      dft_any<R0, +1>(v);
-#pragma unroll
-      for (int q = 0; q < R0; ++q) B[atb(j1 * R0 + q)] = v[q];
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        v[q] = mk<T>(a2[q].x - b2[q].y, a2[q].y + b2[q].x);
-        v[Q + q] = mk<T>(0, 0);
-        const cT c1 = mk<T>(a1[q].x + b1[q].y, -a1[q].y + b1[q].x), c2 = mk<T>(a2[q].x + b2[q].y, -a2[q].y + b2[q].x);
-        v[R0 - 1 - q] = sel(t, c1, c2);
-      }
-      dft_any<R0, +1>(v);
-#pragma unroll
-      for (int q = 0; q < R0; ++q) B[atb(j2 * R0 + q)] = v[q];
-    }
-    __syncthreads();
-    middle(std::integral_constant<int, +1>{}, cntc);
-    if (on) {
-      static_for_stage<0, NC>([&](auto pc) {
-        constexpr int p = decltype(pc)::value;
-        const cT* B = buf + (row * NB2 + p) * LS;
-        cT v[PT];
-#pragma unroll
-        for (int q = 0; q < PT; ++q) v[q] = B[atb(tj + q * TR)];
-        fft_butterfly<L, PT, L / PT, +1, T>(v, tj, tw);
-        take(pc, v);
-      });
-    }
-    __syncthreads();
+  const T sc = (T)0.5 / (T)X::L;
+  auto out = [&](int rw, int ea, int eb) {
+    double2* h = H + (size_t)(r0 + rw) * Px;
+    return XDst{h + (size_t)ea * R * Px, eb < 0 ? nullptr : h + (size_t)eb * R * Px, sc, sc};
   };
-
-  const T sc = (T)0.5 / (T)L;
-  // forward transforms of NC sequences: give(i, v) supplies the PT grid points of
-  // sequence i, ea(i) and eb(i) are its two output fields (eb < 0: one)
-  auto forward = [&](auto cntc, auto&& give, auto&& ea, auto&& eb) __attribute__((always_inline)) {
-    constexpr int NC = decltype(cntc)::value;
-    if (on) {
-      static_for_stage<0, NC>([&](auto pc) {
-        constexpr int p = decltype(pc)::value;
-        cT* B = buf + (row * NB2 + p) * LS;
-        cT v[PT];
-        give(pc, v);
-        dft_any<PT, -1>(v);
-#pragma unroll
-        for (int q = 0; q < PT; ++q) B[atf(tj * PT + q)] = v[q];
-      });
-    }
-    __syncthreads();
-    middle(std::integral_constant<int, -1>{}, cntc);
-    constexpr int IT = NR * NC * U, NB = (IT + NT - 1) / NT;
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int it = tid + b * NT, sq = it / U, t = it - sq * U, rw = sq / NC, p = sq % NC;
-      if (rw >= nrow) continue;
-      const int j1 = t, j2 = t ? W - t : U, r = r0 + rw;
-      const cT* B = buf + (rw * NB2 + p) * LS;
-      cT v1[R0], v2[R0];
-#pragma unroll
-      for (int q = 0; q < R0; ++q) {
-        v1[q] = B[atf(j1 + q * W)];
-        v2[q] = B[atf(j2 + q * W)];
-      }
-      fft_butterfly<L, R0, W, -1, T>(v1, j1, tw);
-      fft_butterfly<L, R0, W, -1, T>(v2, j2, tw);
-      const int fa = ea(p), fb = eb(p);
-      double2* Ha = H + ((size_t)fa * R + r) * Px;
-      double2* Hb = H + ((size_t)(fb < 0 ? fa : fb) * R + r) * Px;
-      auto put = [&](int k, cT z, cT m) {
-        stv<T>(Ha + k, mk<T>(sc * (z.x + m.x), sc * (z.y - m.y)));
-        if (fb >= 0) stv<T>(Hb + k, mk<T>(sc * (z.y + m.y), -sc * (z.x - m.x)));
-      };
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        // partner L - k of k = j + q W
-        put(j1 + q * W, v1[q], sel(t, v2[R0 - 1 - q], v1[q ? R0 - q : 0]));
-        put(j2 + q * W, v2[q], sel(t, v1[R0 - 1 - q], v2[R0 - 1 - q]));
-      }
-      if (t == 0) {  // Nyquist slot
-        stv<T>(Ha + Pa, mk<T>(0, 0));
-        if (fb >= 0) stv<T>(Hb + Pa, mk<T>(0, 0));
-      }
-    }
-    __syncthreads();
-  };
-
-  using One = std::integral_constant<int, 1>;
-  using Two = std::integral_constant<int, 2>;
   if constexpr (DIM == 2) {
-    T u[PT], w[PT], nb[PT], nu[PT], nw[PT];
-    auto take = [&](int pk, const cT* v) __attribute__((always_inline)) {  // pk a constant
+    T u[PT], w[PT], na[PT], nb[PT];
+    auto take = [&](auto kc, const cT* v) __attribute__((always_inline)) {
+      constexpr int K = decltype(kc)::value;  // 0: (u, w); 1, 2: the first, second product
 #pragma unroll
       for (int q = 0; q < PT; ++q) {
-        if (pk == 0) {
+        if (K == 0) {
           u[q] = v[q].x;
           w[q] = v[q].y;
         } else {
-          const T n = -(u[q] * v[q].x + w[q] * v[q].y);
-          if (pk == 1) nb[q] = n;
-          if (pk == 2) nu[q] = n;
-          if (pk == 3) nw[q] = n;
+          (K == 1 ? na : nb)[q] = -(u[q] * v[q].x + w[q] * v[q].y);
         }
       }
     };
-    auto run1 = [&](auto kc) __attribute__((always_inline)) {
-      constexpr int K = decltype(kc)::value;
-      backward(One{}, [](int) { return K; }, [&](auto, const cT* v) { take(K, v); });
-    };
-    auto run2 = [&](auto k0c, auto k1c) __attribute__((always_inline)) {
-      constexpr int K0 = decltype(k0c)::value, K1 = decltype(k1c)::value;
-      if constexpr (NB2 >= 2) {
-        backward(Two{}, [](int p) { return p ? K1 : K0; },
-                 [&](auto pc, const cT* v) { take(decltype(pc)::value ? K1 : K0, v); });
-      } else {
-        run1(k0c);
-        run1(k1c);
-      }
-    };
-    auto giveA = [&](auto, cT* v) {
-#pragma unroll
-      for (int q = 0; q < PT; ++q) v[q] = mk<T>(nb[q], nu[q]);
-    };
-    auto giveB = [&](auto, cT* v) {
-#pragma unroll
-      for (int q = 0; q < PT; ++q) v[q] = mk<T>(nw[q], (T)0);
-    };
-    using K0 = std::integral_constant<int, 0>;
-    using K3 = std::integral_constant<int, 3>;
-    if (blockIdx.y == 0) {
-      run2(K0{}, One{});
-      run1(Two{});
-      forward(One{}, giveA, [](int) { return 0; }, [](int) { return 1; });
+    using One = std::integral_constant<int, 1>;
+    const int k1 = blockIdx.y == 0 ? 1 : 3;  // (b_x, b_z) or (w_x, w_z)
+    if constexpr (NB2 >= 2) {
+      x.template backward<2>([&](int rw, int p) { return pair(rw, p ? k1 : 0); }, take);
     } else {
-      run2(K0{}, K3{});
-      forward(One{}, giveB, [](int) { return 2; }, [](int) { return -1; });
+      x.template backward<1>([&](int rw, int) { return pair(rw, 0); }, take);
+      x.template backward<1>([&](int rw, int) { return pair(rw, k1); }, [&](auto, const cT* v) { take(One{}, v); });
     }
+    if (blockIdx.y == 0) {
+      x.template backward<1>([&](int rw, int) { return pair(rw, 2); },
+                             [&](auto, const cT* v) { take(std::integral_constant<int, 2>{}, v); });
+    } else {
+#pragma unroll
+      for (int q = 0; q < PT; ++q) nb[q] = 0;
+    }
+    x.template forward<1>(
+        [&](auto, cT* v) {
+#pragma unroll
+          for (int q = 0; q < PT; ++q) v[q] = mk<T>(na[q], nb[q]);
+        },
+        [&](int rw, int) { return blockIdx.y == 0 ? out(rw, 0, 1) : out(rw, 2, -1); });
   } else {
     T u[PT], v_[PT], w[PT], nb[PT], nu[PT], nv[PT], nw[PT];
-    static_for_stage<0, 8 / NB2>([&](auto kc) {
+    static_for_stage<0, 8 / NB2>([&](auto kc) __attribute__((always_inline)) {
       constexpr int K = decltype(kc)::value * NB2;
-      backward(std::integral_constant<int, NB2>{}, [](int p) { return K + p; }, [&](auto pc, const cT* v) {
+      x.template backward<NB2>([&](int rw, int p) { return pair(rw, K + p); },
+                               [&](auto pc, const cT* v) __attribute__((always_inline)) {
         constexpr int kk = K + decltype(pc)::value;
 #pragma unroll
         for (int q = 0; q < PT; ++q) {
@@ -780,22 +569,23 @@ __global__ void __launch_bounds__((NR * (PL::L / PL::PT) + 63) / 64 * 64) __attr
         }
       });
     });
-    forward(Two{}, [&](auto pc, cT* v) {
+    x.template forward<2>(
+        [&](auto pc, cT* v) __attribute__((always_inline)) {
 #pragma unroll
-      for (int q = 0; q < PT; ++q) v[q] = decltype(pc)::value ? mk<T>(nv[q], nw[q]) : mk<T>(nb[q], nu[q]);
-    }, [](int p) { return 2 * p; }, [](int p) { return 2 * p + 1; });
+          for (int q = 0; q < PT; ++q) v[q] = decltype(pc)::value ? mk<T>(nv[q], nw[q]) : mk<T>(nb[q], nu[q]);
+        },
+        [&](int rw, int p) { return out(rw, 2 * p, 2 * p + 1); });
   }
 }
 
 template <int DIM, typename PL, int NR, int NB2, int WPE = 2>
 static hipError_t launch_xfft(const XformArgs& a, const void* G, void* H, hipStream_t st) {
   static_assert(DIM == 2 || NB2 >= 2, "the forward transforms run two at a time in 3-D");
-  constexpr size_t lds = (size_t)NR * NB2 * xseq<PL>() * sizeof(double2);
-  constexpr int NT = (NR * (PL::L / PL::PT) + 63) / 64 * 64;
+  using X = XRow<PL, NR, NB2>;
   const int rows = a.M * (DIM == 2 ? 1 : a.Ngy);
   auto fn = xrow_fft_kernel<DIM, PL, NR, NB2, WPE>;
-  allow_lds((const void*)fn, lds);
-  hipLaunchKernelGGL(fn, dim3((rows + NR - 1) / NR, DIM == 2 ? 2 : 1), dim3(NT), lds, st, a, (const double2*)G,
+  allow_lds((const void*)fn, X::lds);
+  hipLaunchKernelGGL(fn, dim3((rows + NR - 1) / NR, DIM == 2 ? 2 : 1), dim3(X::NT), X::lds, st, a, (const double2*)G,
                      (double2*)H, rows);
   return hipGetLastError();
 }

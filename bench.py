@@ -7,9 +7,9 @@ noise on b (workload seed 1002): 33,024 pencil slots (32,640 solved) of
 9 * 128 unknowns, batched into one solve launch.  A step is one pass of the
 whole hot path: the backward z transform, the backward y transform, the x
 pass with the grid products, the forward y transform, the forward z transform
-with the SBDF2 right-hand side, and the banded pencil solve.  The two
-start-up factorisations (SBDF1, then SBDF2) run in the warm-up steps, as in
-any run of the scheme, and are timed and reported on their own.
+with the SBDF2 right-hand side, and the pencil solve.  The solve's factor
+tables of the two operators (SBDF1, then SBDF2) are formed in the warm-up
+steps, as in any run of the scheme, and are timed and reported on their own.
 
 Prints one JSON line: metric, value (DOF-updates/s = 9 Nx Ny Nz per step per
 second), the roofline of the dominant kernel (HIP events on the launch
@@ -86,7 +86,7 @@ def solver(w, precision="fp64", dct="auto", solve="auto", **kw):
                     Ly=w["Ly"], precision=precision, dct=dct, mixed_solve=solve, **kw)
 
 
-def algorithmic_bytes(info, dim):
+def algorithmic_bytes(info, w):
     """Minimum HBM bytes per launch of each kernel (FP64 complex = 16 B): every
     input read once, every output written once.
       z backward: the state fields the explicit term needs (2-D b, u, w, bz,
@@ -100,13 +100,10 @@ def algorithmic_bytes(info, dim):
       z forward + RHS: the explicit term read, the previous state's evolved
         rows and the old history read, the new history (two arrays) and the
         right-hand side written;
-      solve: the whole-band factors (kl + kl + ku + 1 doubles and a pivot
-        byte per column) and the right-hand side read, the state written.
-        This is the banded method's bound; where the solve reads the
-        factors' nonzeros from sparse records it moves fewer bytes than this
-        (roofline.traffic and traffic_frac give what HBM moved)."""
+      solve: the right-hand side and one factor table (10 arrays of N doubles)
+        per distinct wavenumber modulus read, the state written."""
+    dim = w["dim"]
     P, Pa, N, M, S, ne = info["P"], info["P_active"], info["Nz"], info["Ngz"], info["S"], info["ne"]
-    n, kl, ku = info["n"], info["kl"], info["ku"]
     Px, Ny, Ngy = info["Px"], info["Ny"], info["Ngy"]
     c16 = 16
     # state fields read, z-transformed fields, fields of the x pass
@@ -119,7 +116,9 @@ def algorithmic_bytes(info, dim):
         xp = nf * M * Ngy * (Px - 1) * c16 + ne * M * Ngy * Px * c16
         yp = (nz * M * Ny * Px + nf * M * Ngy * Px) * c16 + (ne * M * Ngy * Px + ne * M * Ny * Px) * c16
     zf = ne * M * P * c16 + ne * P * N * c16 + 2 * (2 * ne * P * N * c16) + ne * P * N * c16
-    solve = Pa * n * ((2 * kl + ku + 1) * 8 + 1) + Pa * ne * N * c16 + P * S * N * c16
+    k2 = {(ix / w["Lx"]) ** 2 for ix in range(w["Nx"] // 2)} if dim == 2 else {
+        (ix / w["Lx"]) ** 2 + (iy / w["Ly"]) ** 2 for ix in range(w["Nx"] // 2) for iy in range(w["Ny"] // 2)}
+    solve = len(k2) * 10 * N * 8 + Pa * ne * N * c16 + P * S * N * c16
     out = {"z_backward": zb, "x_pass": xp, "z_forward_rhs": zf, "pencil_solve": solve}
     if yp:
         out["y_pass"] = yp  # backward + forward, summed per step (two launches)
@@ -564,7 +563,7 @@ def main():
     r = run(w, "fp64", steps=args.steps, warmup=args.warmup, timing_steps=args.timing_steps)
     X64 = r.pop("X")
     info = r["info"]
-    nbytes = algorithmic_bytes(info, w["dim"])
+    nbytes = algorithmic_bytes(info, w)
     kernels = {}
     for k, (us, cnt) in r["kernels"].items():
         launches_per_step = cnt / args.timing_steps if args.timing_steps else 1

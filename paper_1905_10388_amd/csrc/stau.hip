@@ -511,6 +511,11 @@ static void free_pencils(stau_pencils* p) {
   hipFree(p->scratch);
 }
 
+// The zeroing of a slot (on the null stream) done before the slot is handed out:
+// the call that allocates it fills it at once on its own stream, which need not
+// be ordered after the null stream.
+static hipError_t zeroing_done() { return hipStreamSynchronize(nullptr); }
+
 // Allocate (zeroed) factor storage for one slot of the band description pa.
 static hipError_t alloc_slot(stau_pencils::FactorSlot& f, const PencilArgs& pa, size_t* bytes,
                              bool fp32 = false) {
@@ -529,6 +534,7 @@ static hipError_t alloc_slot(stau_pencils::FactorSlot& f, const PencilArgs& pa, 
     get((void**)&f.L32raw, cols * pa.FW * sizeof(float));
     get((void**)&f.U32raw, cols * pa.BW * sizeof(float));
   }
+  if (e == hipSuccess) e = zeroing_done();
   if (e != hipSuccess) return e;
   f.Lf = f.Lraw + sk * pa.FW;
   f.Uf = f.Uraw + sk * pa.BW;
@@ -573,6 +579,7 @@ static hipError_t alloc_slot2(stau_pencils::FactorSlot& f, const PencilArgs& pt,
     get((void**)&f.LB32raw, cB * pb.FW * sizeof(float));
     get((void**)&f.UB32raw, cB * pb.BW * sizeof(float));
   }
+  if (e == hipSuccess) e = zeroing_done();
   if (e != hipSuccess) return e;
   if (fp32) {
     f.LfT32 = f.LT32raw + sk * pt.FW;

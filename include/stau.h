@@ -208,7 +208,10 @@ int stau_query(const stau_pencils* pen, stau_info* info);
  * banded LU with partial pivoting (Sec. IX: factorisations are stored and
  * reused while a0, b0 are unchanged).  Synchronises `stream`.  Returns
  * STAU_ESINGULAR if a pivot is zero or non-finite; the first such pencil index
- * is then returned by stau_last_singular_pencil(). */
+ * is then returned by stau_last_singular_pencil().  The operator's factors for
+ * stau_step, stau_step_rk and stau_lbvp (see stau_step) are formed as well: a
+ * call of these with the same (a0, b0) then launches kernels only (it can be
+ * captured into a graph) until two other operators have been factored. */
 int stau_factor(stau_pencils* pen, double a0, double b0, void* stream);
 int64_t stau_last_singular_pencil(const stau_pencils* pen);
 

@@ -1163,7 +1163,11 @@ int stau_factor(stau_pencils* pen, double a0, double b0, void* stream) {
   pen->has_last = rc == STAU_OK;
   pen->last_a0 = a0;
   pen->last_b0 = b0;
-  return rc;
+  if (rc) return rc;
+  // the steps, stages and boundary value solves with this operator find their
+  // tables too: after this call they launch kernels only, as under capture
+  const stau_pencils::TauSlot* t = nullptr;
+  return tau_for(pen, a0, b0, st, &t);
 }
 
 int64_t stau_last_singular_pencil(const stau_pencils* pen) { return pen ? pen->last_sing : -1; }

@@ -1147,6 +1147,7 @@ static int tau_for(stau_pencils* pen, double a0, double b0, hipStream_t st, cons
   set[k].valid = true;
   set[k].a0 = a0;
   set[k].stamp = ++pen->clock;
+  pen->last_sing = -1;
   *out = &set[k];
   return STAU_OK;
 }

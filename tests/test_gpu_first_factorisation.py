@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 if not torch.cuda.is_available():  # pragma: no cover - CPU containers
     pytest.skip("no GPU", allow_module_level=True)
 
-from paper_1905_10388_amd import RBSolver  # noqa: E402
+from paper_1905_10388_amd import RBSolver, StauError  # noqa: E402
 
 # Nx, Ny, Nz
 SHAPES = [(512, 1, 128), (64, 1, 8), (64, 32, 32)]
@@ -72,3 +72,17 @@ def test_first_factorisation_on_a_side_stream(shape, name):
         g.close()
     assert np.isfinite(out[0]).all() and np.abs(out[0]).max() > 0
     assert np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("gamma", [(), (0.3,)], ids=["tridiagonal", "banded"])
+def test_singular_pencil_is_forgotten_by_the_next_factorisation(gamma):
+    """stau_last_singular_pencil names the pencil of a failed factorisation
+    until one succeeds, in a step as in the component call, whatever form of
+    factors the step's operator has."""
+    g = RBSolver(16, 8, 4.0, 1e4, 1.0, gamma=gamma)
+    for ok in (lambda: g.step(1e-3), lambda: g.factor(1e3)):
+        with pytest.raises(StauError, match="SINGULAR"):
+            g.factor(0.0, 0.0)
+        assert g.last_singular_pencil() >= 0
+        ok()
+        assert g.last_singular_pencil() == -1

@@ -85,18 +85,25 @@ constexpr int kTauThreads = 256;
 __global__ void __launch_bounds__(kTauThreads) tau_factor_kernel(int N, int lgN, int nk, int KB, double a0,
                                                                  double kappa, double nu,
                                                                  const double* __restrict__ kmod,
-                                                                 double* __restrict__ tab, double* __restrict__ scal) {
+                                                                 double* __restrict__ tab, double* __restrict__ scal,
+                                                                 [[maybe_unused]] unsigned* check) {
   extern __shared__ double lds[];
   const int tid = threadIdx.x;
   const int k0 = blockIdx.x * KB, nkb = min(KB, nk - k0);
   const int KS = (kTauArrays + kTauWork) * N + kTauScal + 1;  // stride per wavenumber
   const int n = N / 2;
   double* inv = lds + (size_t)KB * KS;                        // 1 / m
-  auto T_of = [&](int kb) { return lds + (size_t)kb * KS; };
+  auto T_of = [&](int kb) {
+    STAU_BOUND(check, kb >= 0 && kb < KB && k0 + kb < nk, kChkTau);
+    return lds + (size_t)kb * KS;
+  };
   auto sc_of = [&](int kb) { return lds + (size_t)kb * KS + (kTauArrays + kTauWork) * N; };
   // f(kb, m) for every wavenumber and degree
   auto each = [&](auto&& f) {
-    for (int idx = tid; idx < nkb << lgN; idx += kTauThreads) f(idx >> lgN, idx & (N - 1));
+    for (int idx = tid; idx < nkb << lgN; idx += kTauThreads) {
+      STAU_BOUND(check, idx >> lgN < nkb && (1 << lgN) == N, kChkTau);
+      f(idx >> lgN, idx & (N - 1));
+    }
   };
   for (int m = tid + 1; m <= N; m += kTauThreads) inv[m] = 1.0 / (double)m;
   if (tid < nkb) sc_of(tid)[kScK] = kmod[k0 + tid];
@@ -434,15 +441,27 @@ __global__ void __launch_bounds__(E > 8 ? 512 : 256) tau_solve_kernel(PencilArgs
   double2* gauge = (double2*)(starts + 4 * NP);    // the mean pencil's sum of p over degrees >= 1
   double* base = (double*)(gauge + 1);
   // chain ch = 2 parity + part of an array; coefficients by parity
-  auto chain_at = [&](int i, int which, int ch) { return base + (size_t)i * PS + (which * 4 + ch) * PL; };
-  auto coef_at = [&](int i, int which, int c) { return base + (size_t)i * PS + (NA * 4 + which * 2 + c) * PL; };
-  auto pos = [](int m) { return (m >> 1) + (m >> 1) / E; };
+  auto chain_at = [&](int i, int which, int ch) {
+    STAU_BOUND(a.check, i >= 0 && i < NP && which < NA && ch < 4, kChkTau);
+    return base + (size_t)i * PS + (which * 4 + ch) * PL;
+  };
+  auto coef_at = [&](int i, int which, int c) {
+    STAU_BOUND(a.check, i >= 0 && i < NP && which < 4 && c < 2, kChkTau);
+    return base + (size_t)i * PS + (NA * 4 + which * 2 + c) * PL;
+  };
+  // place of degree m in its chain
+  auto pos = [&](int m) {
+    const int o = (m >> 1) + (m >> 1) / E;
+    STAU_BOUND(a.check, m >= 0 && m < N && o < PL, kChkTau);
+    return o;
+  };
 
   // this thread's pencil and degree
   const int i = tid / N, m = tid - i * N, p = (int)blockIdx.x * NP + i;
   const bool mine = i < NP && p < a.P;
   const int slot = mine ? tf.slot[p] : -1;
   const bool on = slot >= 0;
+  STAU_BOUND(a.check, slot < tf.nk, kChkTau);
   const double* T = tf.tab + (size_t)(on ? slot : 0) * (kTauArrays * N) + m;
   const double* sc = tf.scal + (size_t)(on ? slot : 0) * kTauScal;
   const double2 zero = make_double2(0.0, 0.0);
@@ -506,6 +525,8 @@ __global__ void __launch_bounds__(E > 8 ? 512 : 256) tau_solve_kernel(PencilArgs
   const int lslot = li < NP && lp < a.P ? tf.slot[lp] : -1;
   const double* lsc = tf.scal + (size_t)(lslot >= 0 ? lslot : 0) * kTauScal;
   auto chain = [&](int s, int f, int w, int sys, int which, double G) {
+    // (its degrees, and the next lane's first where there is one)
+    STAU_BOUND(a.check, g >= 0 && g < L && L * E == N / 2 && g * (E + 1) + E <= PL && lslot < tf.nk, kChkTau);
     tau_chain<E>(chain_at(li, s, ch & 3), chain_at(li, f, ch & 3), coef_at(li, w, c), coef_at(li, w + 1, c),
                  lsc + kScSys + 3 * sys, G, g, L, c, part, starts + li * 4 + which);
   };
@@ -670,7 +691,7 @@ hipError_t launch_tau_factor(const PencilArgs& a, double a0, const TauFactors& t
   while ((1 << lgN) < N) ++lgN;
   allow_lds((const void*)tau_factor_kernel, lds);
   hipLaunchKernelGGL(tau_factor_kernel, dim3((tf.nk + KB - 1) / KB), dim3(kTauThreads), lds, st, N, lgN, tf.nk, KB, a0,
-                     a.kappa, a.nu, tf.k, tf.tab, tf.scal);
+                     a.kappa, a.nu, tf.k, tf.tab, tf.scal, a.check);
   return hipGetLastError();
 }
 

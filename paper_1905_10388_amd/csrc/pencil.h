@@ -15,7 +15,7 @@ constexpr int kWave = 64;
 // Index checks of the check build (STAU_CHECK_BOUNDS): a failed check sets
 // its bit in the pencils' check word (read by stau_check); no trap, and
 // nothing at all in other builds.
-enum CheckBits : unsigned { kChkPivot = 1u, kChkRecord = 2u, kChkSlot = 4u, kChkRank = 8u };
+enum CheckBits : unsigned { kChkPivot = 1u, kChkRecord = 2u, kChkSlot = 4u, kChkRank = 8u, kChkTau = 16u };
 #ifdef STAU_CHECK_BOUNDS
 #define STAU_BOUND(word, cond, bit)              \
   do {                                           \

@@ -1762,7 +1762,8 @@ int stau_check(stau_pencils* pen, const void* X, void* stream) {
   HIP_TRY(hipMemcpy(&bits, pen->check, sizeof(unsigned), hipMemcpyDeviceToHost));
   if (bits)
     return fail(STAU_EBOUNDS, "index check failed since the pencils were built (bits 0x%x: 1 pivot offset, "
-                "2 sparse record size, 4 forward-window slot, 8 record rank)", bits);
+                "2 sparse record size, 4 forward-window slot, 8 record rank, 16 table or place of the "
+                "tridiagonal solve)", bits);
 #endif
   return STAU_OK;
 }

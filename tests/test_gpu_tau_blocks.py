@@ -15,7 +15,11 @@ number of pencil slots (every 2-D shape).
   inactive slots zero.
 * That solve and an SBDF1 step against the oracle on pencils at every place of
   the first block and of the last ones, per pencil, 1e-10 relative: the FP64
-  bar of the other solve tests."""
+  bar of the other solve tests.
+* The check build (index checks of the kernels compiled in) on the same calls:
+  every check holds, the values are the default library's within 1e-13."""
+import os
+
 import numpy as np
 import pytest
 
@@ -29,7 +33,7 @@ pytestmark = pytest.mark.gpu
 if not torch.cuda.is_available():  # pragma: no cover - CPU containers
     pytest.skip("no GPU", allow_module_level=True)
 
-from paper_1905_10388_amd import RBSolver  # noqa: E402
+from paper_1905_10388_amd import RBSolver, _lib  # noqa: E402
 
 BAR = 1e-10
 DT = 1e-3
@@ -71,10 +75,10 @@ def _box(dim, Nx):
     return dict(Lx=max(4.0, Nx / 32.0), Ly=3.0)
 
 
-def _solver(shape):
+def _solver(shape, library="default"):
     dim, Nx, Ny, Nz = shape
     b = _box(dim, Nx)
-    return RBSolver(Nx, Nz, b["Lx"], 1e5, 0.7, dim=dim, Ny=Ny, Ly=b["Ly"])
+    return RBSolver(Nx, Nz, b["Lx"], 1e5, 0.7, dim=dim, Ny=Ny, Ly=b["Ly"], library=library)
 
 
 def _run(g, X0, F):
@@ -117,3 +121,19 @@ def test_block_forms(shape):
     for X, ref in ((Xb, o.lbvp(F)), (Xs, o.step(X0, DT))):
         for key, *_ in sample:
             assert rel_err(X[key], ref[key]) < BAR, (key, rel_err(X[key], ref[key]))
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "-".join(str(v) for v in s))
+def test_block_forms_in_the_check_build(shape):
+    if not os.path.exists(_lib.LIB_CHECK_PATH):  # pragma: no cover
+        pytest.skip("libstau_check.so not built (__graft_entry__.build() builds it)")
+    out = []
+    for library in ("check", "default"):
+        g = _solver(shape, library)
+        X0, F = _field(g.state_shape, 142), _field(g.state_shape, 143)[..., :g.info["ne"], :].copy()
+        r = _run(g, X0, F)
+        g.check()
+        out.append(r)
+        g.close()
+    for a, b in zip(*out):
+        assert np.linalg.norm(a - b) <= 1e-13 * np.linalg.norm(b)

@@ -357,9 +357,10 @@ int stau_solve(stau_pencils* pen, const void* B_ev, void* X, void* stream);
  * (libstau_check.so, compiled with STAU_CHECK_BOUNDS) the kernels also record
  * index checks (the factorisation's pivot offsets within the band, the
  * forward sweeps' window slots, the sparse factor records' sizes and ranks,
- * the tridiagonal solve's tables, chains and LDS places) in a word per pencils object; stau_check then returns STAU_EBOUNDS if any
- * failed since stau_build_pencils.  A failed check never traps: the kernels
- * carry on, and the result of that call is not to be trusted. */
+ * the tridiagonal solve's tables, chains and LDS places) in a word per pencils
+ * object; stau_check then returns STAU_EBOUNDS if any failed since
+ * stau_build_pencils.  A failed check never traps: the kernels carry on, and
+ * the result of that call is not to be trusted. */
 int stau_check(stau_pencils* pen, const void* X, void* stream);
 
 /* Kinetic-energy functional J = (1/V) int |u|^2 / 2 evaluated on the 3/2 grid

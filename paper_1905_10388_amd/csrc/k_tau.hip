@@ -335,10 +335,9 @@ __device__ __forceinline__ double chain_enter(double v, double& pi, int g, int L
   return edge ? 0.0 : in;
 }
 
-// What a chain leaves beside q and its fluxes: first flux, q_0 (even q), sum of
-// the fluxes
+// What a chain leaves beside q and its fluxes: first flux, sum of the fluxes
 struct TauStart {
-  double2 f[2], q0, sum[2];
+  double2 f[2], sum[2];
 };
 
 // One chain with boundary sum G: S (ratio_{m+2} fh_m) becomes q, F the fluxes;

@@ -618,7 +618,7 @@ def main():
             m["dtype"] = "f32+f64"
             m["z_transform"] = "split-BF16 matrix-core products" if dct == "matmul" else "FP32 FFT"
             m["pencil_solve"] = ("FP32 sweeps + one FP64 refinement" if solve == "refined"
-                                 else "FP64 sweeps")
+                                 else "FP64")
             m["diff_vs_fp64_per_field"] = field_err(Xmx, X64, 3)
             m["steps_compared"] = r["warmup"] + args.steps
             m["speedup_vs_fp64"] = rmx["value"] / r["value"]

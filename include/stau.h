@@ -106,7 +106,7 @@ typedef struct stau_pencils stau_pencils;
  *          STAU_DCT_AUTO takes them for Nz = 64; otherwise the mixed step
  *          uses the FP32 FFT.
  * mixed_solve  the pencil solve of the mixed-precision steps (ignored in
- *          FP64 domains): STAU_SOLVE_FP64 (FP64 sweeps on the FP64 factors),
+ *          FP64 domains): STAU_SOLVE_FP64 (the solve that FP64 domains use),
  *          STAU_SOLVE_REFINED (FP32 sweeps on FP32 copies of the FP64
  *          factors, the residual of the first solution in FP64 from the
  *          operator templates, one FP32 correction sweep, the sum in FP64; in
@@ -208,10 +208,12 @@ int stau_query(const stau_pencils* pen, stau_info* info);
  * banded LU with partial pivoting (Sec. IX: factorisations are stored and
  * reused while a0, b0 are unchanged).  Synchronises `stream`.  Returns
  * STAU_ESINGULAR if a pivot is zero or non-finite; the first such pencil index
- * is then returned by stau_last_singular_pencil().  The operator's factors for
- * stau_step, stau_step_rk and stau_lbvp (see stau_step) are formed as well: a
- * call of these with the same (a0, b0) then launches kernels only (it can be
- * captured into a graph) until two other operators have been factored. */
+ * is then returned by stau_last_singular_pencil().  Pencils whose steps do not
+ * read these factors (see stau_step) allocate the storage here, one operator's
+ * in each of the first two calls: STAU_ENOMEM if it does not fit the device.
+ * The operator's factors for stau_step, stau_step_rk and stau_lbvp are formed
+ * as well: a call of these with the same (a0, b0) then launches kernels only
+ * (it can be captured into a graph), until two other operators are factored. */
 int stau_factor(stau_pencils* pen, double a0, double b0, void* stream);
 int64_t stau_last_singular_pencil(const stau_pencils* pen);
 
@@ -225,8 +227,10 @@ int64_t stau_last_singular_pencil(const stau_pencils* pen);
  * Without a non-constant coefficient (and unless mixed_solve is
  * STAU_SOLVE_REFINED) the pencil systems of the steps, the Runge-Kutta stages
  * and stau_lbvp are solved exactly reduced to tridiagonal systems, whose
- * factors are kept apart from those of stau_factor; the banded factors'
- * storage is then allocated by the first call that needs it. */
+ * factors (allocated with the pencils) are kept apart from the banded ones that
+ * stau_solve reads; the banded factors' storage is then allocated by the first
+ * call that needs it (stau_factor, or a step whose a0 is beyond 1e100 times the
+ * smaller diffusivity). */
 int stau_step(stau_pencils* pen, stau_state* st, double dt, void* stream);
 
 /* One IMEX Runge-Kutta step X^n -> X^{n+1} (Sec. IX "Runge-Kutta IMEX

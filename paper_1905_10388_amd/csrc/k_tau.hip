@@ -33,9 +33,12 @@
 // every coefficient is a ratio of sums of positive terms (S an average of fh),
 // so nothing cancels in the factors, and q and qz come out together, each
 // accurate in its own scale.  The boundary row sum q = G fixes the first flux.
-// Against 80-bit solutions of random right-hand sides over k <= 6400, dt >= 1e-5,
-// N <= 128 the error per field is 6e-16 in the median and 2.3e-13 at most,
-// where a dense LU with partial pivoting has 7e-15 and 1e-10.
+// Against 80-bit solutions over k <= 6400, dt >= 1e-5 the worst field's error is
+//   random right-hand sides (N <= 128):   6e-16 in the median, 2.3e-13 at most
+//     (a dense LU with partial pivoting: 7e-15 and 1e-10);
+//   a step's (a0 M X of an admissible state outweighs the rest, N <= 64):
+//     1e-13 in the median, 5e-10 at most (LU 2e-13 and 5e-10), for both in bz,
+//     uz and p; b, U, w and wz stay within 4e-15 (LU 2.5e-11).
 //
 // Factor tables per distinct wavenumber modulus k (a 3-D domain of a square
 // box has one for up to eight pencils), kTauArrays arrays of N doubles: ratio and

@@ -620,7 +620,11 @@ static hipError_t launch_xfft_L(const XformArgs& a, const void* G, void* H, hipS
       case 6144: return launch_xfft<2, FftPlan<6, 16, 8, 8>, 1, 1, 3>(a, G, H, st);
     }
   } else {
-    // few rows: all eight pairs at once, four rows per block
+    // few rows: all eight pairs at once, four rows per block.  Events on the launch
+    // stream, this plan against the other (us): 24 points at 576 / 2304 / 4608 /
+    // 9216 / 36864 rows 6.8 / 7.7 / 10.3 / 14.2 / 25.7 against 8.9 / 9.6 / 11.1 /
+    // 14.2 / 23.4, 48 points 8.2 / 10.5 / 15.0 / 18.4 / 43.7 against 10.0 / 11.5 /
+    // 15.7 / 16.2 / 43.5: the two cross between 4608 and 9216 rows
     const bool few = a.M * a.Ngy < 4096;
     switch (a.L) {
       case 24:

@@ -1105,8 +1105,8 @@ static int factor_into(stau_pencils* pen, stau_pencils::FactorSlot* set, const P
   return STAU_OK;
 }
 
-// Factors for (a0, b0): a cached slot if one matches, else refactor the least
-// recently used slot (two slots: the SBDF1 and SBDF2 operators of a run).
+// Banded factors for (a0, b0): a cached slot if one matches, else refactor the
+// least recently used slot (two slots: the SBDF1 and SBDF2 operators of a run).
 // trans selects the factors of the transposed matrices (allocated on first use).
 static int factors_for(stau_pencils* pen, double a0, double b0, hipStream_t st,
                        stau_pencils::FactorSlot** out, bool trans = false) {
@@ -1635,7 +1635,8 @@ int stau_solve(stau_pencils* pen, const void* B_ev, void* X, void* stream) {
   if (!pen->has_last) return fail(STAU_ESTATE, "stau_solve before a successful stau_factor");
   HIP_TRY(hipSetDevice(pen->dom->d.device));
   // the slot stau_factor filled may have been refactored since for another
-  // operator (the step's and the boundary value solve's cache is shared)
+  // operator (by a later stau_factor, or by the steps and boundary value solves
+  // of pencils whose solves are banded)
   stau_pencils::FactorSlot* f = nullptr;
   {
     int rc = factors_for(pen, pen->last_a0, pen->last_b0, (hipStream_t)stream, &f);
